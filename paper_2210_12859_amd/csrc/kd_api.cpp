@@ -263,6 +263,8 @@ kd_status resolve_plan(kd_tree t, int k, float maxRadius, const kd_opts* o, Quer
         // paper's count when visited is requested
         if (use.prune == 2) use.prune = 0;
     }
+    p.plain = (use.block == 0 || use.block == 256) && use.lds_levels <= 0 && use.sort_bits < 0 && use.waves_per_cu == 0 &&
+              use.heavy_trips == 0 && use.prune == 0;
     if (use.block == 0) use.block = 256;
     if (use.lds_levels < 0) use.lds_levels = 0;
     if (use.sort_bits < 0) use.sort_bits = 16;

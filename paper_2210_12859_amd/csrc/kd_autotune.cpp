@@ -53,6 +53,7 @@ kd_status kd_autotune(kd_tree t, const float* sample_q, int64_t Qs, int k, float
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const int K = k_template(k);
     std::vector<kd_opts> cands;
+    cands.push_back(kd_opts{256, -1, -1, 0, 0, 0});  // the defaults: the kernel follows from the call's size
     const int blocks[] = {256, 512, 1024};
     const int waves[] = {8, 12, 16, 24, 32};
     const int sorts[] = {0, 16, 24, 32};

@@ -158,6 +158,7 @@ struct QueryPlan {
     int heavy_trips = 0;  // trip budget before the cooperative hand-off, 0 = none
     bool heavy_default = true;  // the budget was left at its default
     int prune = 0;        // kd_opts.prune: 0 default, 1 split planes, 2 subtree boxes
+    bool plain = false;   // every option at its default: the call's kernel follows from its size
 };
 int k_template(int k);
 
@@ -256,6 +257,16 @@ struct FixedScratch {
     void* ptr;
     size_t bytes;
 };
+// kNN with one wave per query (kd_wave.hip).
+struct WaveCall {
+    const float* queries;  // [n][dim]
+    uint32_t n;
+    int k;
+    float R2;
+    int32_t* out_idx;
+    float* out_d2;
+};
+hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, int grid, hipStream_t st);
 // Range queries (kd_traverse.hip): box = false, queries_or_boxes holds
 // float [Q][dim] points and R2 the squared radius; box = true, it holds float
 // [Q][2][dim] boxes.  Writes out_count[Q] and, for cap > 0, out_idx[Q][cap]

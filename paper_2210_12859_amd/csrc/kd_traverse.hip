@@ -57,13 +57,11 @@
 #include <type_traits>
 
 #include "kd_internal.h"
-
+#include "kd_list.h"
 
 namespace kd {
 
 namespace {
-
-constexpr uint32_t SENT_IDX = 0x7fffffffu;
 
 struct TravArgs {
     const void* nodes;       // TreeRec<D>[N + 2], record of node id i at index i
@@ -94,48 +92,6 @@ struct TravArgs {
     uint32_t* heavy_count;   // rows that asked for a hand-off (zero at launch; may exceed heavy_cap)
     int32_t* heavy_rows;     // [heavy_cap] caller rows handed off
 };
-
-// Wave votes on a lane predicate held as a lane mask (no round trip through
-// a VGPR, as the int-argument forms take).
-__device__ __forceinline__ uint64_t wave_ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-__device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
-
-__device__ __forceinline__ uint64_t make_key(float d2, int32_t idx) {
-    return (uint64_t(__float_as_uint(d2)) << 32) | uint32_t(idx);
-}
-
-__device__ __forceinline__ float key_d2(uint64_t key) { return __uint_as_float(uint32_t(key >> 32)); }
-
-// 64-bit keys as doubles: the bit patterns of non-negative doubles order like
-// unsigned integers, and no key reaches the exponent of infinity (the high
-// word is at most that of a binary32 infinity), so v_min_f64 / v_max_f64 take
-// the smaller / larger key in one instruction each (denormal patterns pass
-// unchanged).
-__device__ __forceinline__ uint64_t key_min(uint64_t a, uint64_t b) {
-    uint64_t r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ uint64_t key_max(uint64_t a, uint64_t b) {
-    uint64_t r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-// Sorted insertion of `key` into the ascending list L (its largest key drops
-// out; a key above it changes nothing): slot j becomes key clamped to
-// [L[j-1], L[j]], two instructions.  The network runs for the whole wave
-// whenever a lane inserts, and the step kernels are bound by vector
-// instructions; against the median of the high words plus a 64-bit compare
-// and two selects (four instructions a slot), calls of 1M 3-D queries: k = 8
-// 0.721 -> 0.691 ms, with split planes only 0.712 -> 0.659 ms; 150K 2-D
-// queries, k = 50: 0.885 -> 0.666 ms.
-template <int K>
-__device__ __forceinline__ void list_insert(uint64_t (&L)[K], uint64_t key) {
-#pragma unroll
-    for (int j = K - 1; j > 0; --j) L[j] = key_max(L[j - 1], key_min(key, L[j]));
-    L[0] = key_min(key, L[0]);
-}
 
 // Split dimension of node id n (1-based) is level mod D with level =
 // 31 - clz(n).  DimSel holds the one-hot flags dim == j (j = 1..D-1), read
@@ -1597,6 +1553,20 @@ struct StageEvents {
 };
 }  // namespace
 
+// Calls of at most this many queries go one wave per query: their time there
+// is the launch and one query's chain of group loads until the waves fill the
+// GPU (1.6 ns a query after that), while a lane-by-lane call costs the sort
+// (6 launches) and the longest lane's chain of node loads (80-900 us)
+// however few its queries.  Uniform points, lane by lane -> by wave, us:
+// 10K 3-D points, k = 8: 250 queries 156 -> 13, 65,536 183 -> 95, 262,144
+// 227 -> 344; 1M 3-D points, k = 32: 250 437 -> 25, 262,144 622 -> 841,
+// k = 64: 262,144 1706 -> 1392; 200K 4-D points, k = 8: 65,536 373 -> 168,
+// 262,144 494 -> 570; 200K 2-D points (short chains), k = 1: 65,536 76 -> 51,
+// 262,144 101 -> 189, k = 64: 65,536 386 -> 270, 262,144 892 -> 1029.
+static int64_t wave_queries(int dim, int K) {
+    return (dim == 2 ? int64_t(1) << 16 : int64_t(1) << 17) * (K > 32 ? 2 : 1);
+}
+
 kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& plan, int32_t* out_idx,
                   float* out_d2, uint32_t* visited, kd_stream stream, const LearnedSpec* learned,
                   kd_stats* stats, const FixedScratch* fixed) {
@@ -1617,6 +1587,26 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
     // longer (gmm64-1m k = 8: 1.53 ms at 1024, 1.33 ms at 4096)
     const int heavy_trips = plan.heavy_default && use_boxes ? KD_DEFAULT_HEAVY_TRIPS_BOXES : plan.heavy_trips;
     const bool handoff = heavy_trips > 0 && visited == nullptr;
+    kd_status s = KD_OK;
+    // few queries: one wave each (no scratch, one launch)
+    const bool plain = plan.plain && !visited && !learned;
+    if (plain && Q <= wave_queries(t->dim, plan.K)) {
+        hipEvent_t ev = nullptr;
+        if (!fixed) {
+            s = timing_begin(st, &ev);
+            if (s != KD_OK) return s;
+        }
+        WaveCall wc = {};
+        wc.queries = queries;
+        wc.n = uint32_t(Q);
+        wc.k = plan.k;
+        wc.R2 = plan.R2;
+        wc.out_idx = out_idx;
+        wc.out_d2 = out_d2;
+        const hipError_t we = launch_knn_wave(t, wc, int(Q), st);
+        if (we != hipSuccess) return hip_error(we, "knn_wave launch");
+        return timing_end(st, ev, "traverse");
+    }
     const size_t cursor_bytes = size_t(MAX_GROUPS) * CURSOR_STRIDE * 4;  // 256 KB
     const size_t head = cursor_bytes + 4096;
     const size_t sq_bytes = (size_t(Q) * rec_bytes(t->dim) + 255) & ~size_t(255);
@@ -1624,7 +1614,6 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
     const size_t q4 = (size_t(Q) * 4 + 255) & ~size_t(255);
     const size_t learn_bytes = learned ? 2 * q4 : 0;  // initial radii, start nodes
     const size_t ws_bytes = query_scratch_bytes(Q, t->dim, plan.sort_bits > 0, learned != nullptr, handoff);
-    kd_status s = KD_OK;
     if (fixed) {
         if (ws_bytes > fixed->bytes)
             return set_error(KD_EINVAL, "query scratch of " + std::to_string(ws_bytes) +

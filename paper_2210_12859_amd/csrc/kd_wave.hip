@@ -1,0 +1,228 @@
+// kd_wave.hip -- kNN with one wave per query: the answer's latency instead of
+// its throughput.
+//
+// For calls with too few queries to fill the GPU with one lane each.  A
+// lane-by-lane walk is a chain of ~130 dependent node loads; here the wave's 64
+// lanes share the query:
+//   * groups of levels (kd_groups.h): lane l tests the bounding box of child
+//     group l % 32, so one load descends five levels;
+//   * 64 points at a time (two leaves, one in each half of the wave), one lane
+//     each: squared distances as everywhere (binary32, left to right), and
+//     a vote for those that can enter the list;
+//   * the k-best list lies across the lanes (lane i: the i-th smallest
+//     (d2, index) key, so any k <= 64), an insertion is one shift of the lanes
+//     behind its place.
+// Children are taken nearest first and again tested against the current k-th
+// distance; a group's own points come after its children, when the radius is
+// small.  Box distances are computed like point distances and rounding is
+// monotone, so no point of the result is passed over (ties included): rows are
+// the lane-by-lane traversal's, bit for bit.
+//
+// Bound by the latency of the group and point loads (a k = 8 query over 10K
+// 3-D points: 6 box loads and about 8 pairs of leaves in sequence), then by
+// vector issue once ~8 waves per SIMD run.  250 queries over 10K points, k =
+// 8: 156 us lane by lane (sort, walk, hand-off: 8 launches), 13 us here.
+#include <hip/hip_runtime.h>
+
+#include "kd_groups.h"
+#include "kd_internal.h"
+#include "kd_list.h"
+
+namespace kd {
+
+namespace {
+
+struct WaveArgs {
+    const void* nodes;       // TreeRec<D>[N + 2]
+    const float* boxes;      // subtree boxes by node id
+    int32_t N;
+    GroupShape shape;
+    const float* queries;    // caller [n][D]
+    uint32_t n;
+    int k;
+    float R2;
+    int32_t* out_idx;
+    float* out_d2;
+};
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t old, uint32_t v) {
+    return uint32_t(__builtin_amdgcn_update_dpp(int(old), int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ uint32_t min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
+
+// Smallest of lanes 0-31, wave-uniform.
+__device__ __forceinline__ uint32_t min_low_half(uint32_t v) {
+    v = min_u32(v, dpp_u32<0xb1>(v, v));   // quad_perm 1,0,3,2
+    v = min_u32(v, dpp_u32<0x4e>(v, v));   // quad_perm 2,3,0,1
+    v = min_u32(v, dpp_u32<0x141>(v, v));  // row_half_mirror
+    v = min_u32(v, dpp_u32<0x140>(v, v));  // row_mirror
+    const uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+    return a < b ? a : b;
+}
+
+template <int D>
+__global__ __launch_bounds__(64) void knn_wave(WaveArgs a) {
+    __shared__ float s_gap[MAX_GROUP_LEVELS][64];
+    const TreeRec<D>* __restrict__ g1 = reinterpret_cast<const TreeRec<D>*>(a.nodes);
+    const int32_t* __restrict__ ids =
+        rec_has_idx(D) ? nullptr : reinterpret_cast<const int32_t*>(g1 + (int64_t(a.N) + 2));
+    const uint32_t lane = __lane_id();
+    const bool upper = lane >= 32;
+    // chunk slot of the lane (see kd_groups.h)
+    const int32_t slot = int32_t(lane & 31u);
+    const int32_t slot_lv = slot ? 31 - __builtin_clz(uint32_t(slot)) : 0;
+    const int32_t slot_off = slot - (1 << slot_lv);
+    const int32_t top_levels = a.shape.top_levels, leaf_group = a.shape.leaf_group;
+    const bool six = a.shape.leaf_levels > GL;
+
+    for (uint32_t i = blockIdx.x; i < a.n; i += gridDim.x) {
+        float q[D];
+#pragma unroll
+        for (int j = 0; j < D; ++j) q[j] = a.queries[size_t(i) * D + j];
+        bool ordered = true;  // no NaN
+#pragma unroll
+        for (int j = 0; j < D; ++j) ordered = ordered & (q[j] == q[j]);
+
+        uint64_t key = make_key(a.R2, SENT_IDX);  // lane i: the i-th smallest
+        float worst = a.R2;                        // wave-uniform
+
+        // 64 points, one a lane; the candidates enter one by one
+        auto take = [&](const int32_t r0, const int32_t lv0, const bool six0, const int32_t r1, const int32_t lv1,
+                        const bool six1) {
+            const int32_t r = upper ? r1 : r0, lv = upper ? lv1 : lv0;
+            const bool sx = upper ? six1 : six0;
+            const int32_t id = sx ? (r << GL) + slot : (r << slot_lv) + slot_off;
+            const bool ok = (sx | ((slot > 0) & (slot_lv < lv))) & (r != 0) & (id <= a.N);
+            float p[D];
+            int32_t idx;
+            load_point<D>(g1, ids, ok ? id : 1, p, idx);
+            const float dx0 = q[0] - p[0];
+            float d2 = dx0 * dx0;
+#pragma unroll
+            for (int j = 1; j < D; ++j) {
+                const float dx = q[j] - p[j];
+                d2 = d2 + dx * dx;
+            }
+            uint64_t cand = wave_ballot(ok & (d2 <= worst));
+            while (cand) {
+                const int l = __builtin_ctzll(cand);
+                cand &= cand - 1;
+                const uint64_t ck = (uint64_t(__builtin_amdgcn_readlane(__float_as_uint(d2), l)) << 32) |
+                                    __builtin_amdgcn_readlane(uint32_t(idx), l);
+                // lanes before its place keep their key, the lane there takes
+                // it, the lanes behind take their neighbour's
+                const uint64_t below = wave_ballot(key < ck);
+                const uint32_t at = uint32_t(__popcll(below));
+                if (at >= uint32_t(a.k)) continue;
+                const uint32_t sh = dpp_u32<0x138>(0, uint32_t(key >> 32));  // wave_shr:1
+                const uint32_t sl = dpp_u32<0x138>(0, uint32_t(key));
+                const uint64_t moved = (uint64_t(sh) << 32) | sl;
+                key = lane < at ? key : (lane == at ? ck : moved);
+                worst = __uint_as_float(__builtin_amdgcn_readlane(uint32_t(key >> 32), a.k - 1));
+                cand &= wave_ballot(d2 <= worst);
+            }
+        };
+
+        if (ordered && leaf_group == 0) {
+            take(1, GL, false, six && (1 << GL) <= a.N ? 1 : 0, GL, true);
+        } else if (ordered) {
+            uint32_t stack = 0;  // lane g: children of group level g still to visit
+            int32_t g = 0, r = 1;
+            bool fresh = true;   // the group at hand was just entered
+            float gap = 0.0f;
+            for (;;) {
+                const int32_t lv = g == 0 ? top_levels : GL;
+                uint32_t m;
+                if (fresh) {
+                    float bl[D], bh[D];
+                    const bool none = (slot >> lv) != 0;
+                    load_box<D>(a.boxes, none ? r : (r << lv) + slot, bl, bh);
+                    gap = box_gap<D>(bl, bh, q, q);
+                    m = uint32_t(wave_ballot(!none & (gap <= worst)));
+                } else {
+                    gap = s_gap[g][lane];
+                    m = __builtin_amdgcn_readlane(stack, uint32_t(g)) & uint32_t(wave_ballot(gap <= worst));
+                }
+                if (g + 1 == leaf_group) {
+                    // leaves nearest first, two chunks at a time, then the
+                    // group's own points
+                    int32_t part = 0;
+                    bool own = true;
+                    const uint32_t order = (__float_as_uint(gap) & ~31u) | uint32_t(slot);
+                    while (m | uint32_t(part) | uint32_t(own)) {
+                        int32_t cr[2] = {0, 0}, cl[2] = {GL, GL};
+                        bool cs[2] = {false, false};
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            if (part) {
+                                cr[h] = part;
+                                cs[h] = true;
+                                part = 0;
+                            } else if (m) {
+                                const uint32_t best = min_low_half((m >> slot) & 1u ? order : ~0u) & 31u;
+                                m &= ~(1u << best);
+                                cr[h] = (r << lv) + int32_t(best);
+                                if (six && (cr[h] << GL) <= a.N) part = cr[h];
+                            } else if (own) {
+                                own = false;
+                                cr[h] = r;
+                                cl[h] = lv;
+                            }
+                        }
+                        take(cr[0], cl[0], cs[0], cr[1], cl[1], cs[1]);
+                        m &= uint32_t(wave_ballot(gap <= worst));
+                    }
+                } else if (m) {
+                    if (fresh) s_gap[g][lane] = gap;
+                    const uint32_t order = (__float_as_uint(gap) & ~31u) | uint32_t(slot);
+                    const uint32_t best = min_low_half((m >> slot) & 1u ? order : ~0u) & 31u;
+                    stack = lane == uint32_t(g) ? m & ~(1u << best) : stack;
+                    r = (r << lv) + int32_t(best);
+                    ++g;
+                    fresh = true;
+                    continue;
+                } else {
+                    take(r, lv, false, 0, 0, false);
+                }
+                // the group is done
+                if (g == 0) break;
+                --g;
+                r >>= g == 0 ? top_levels : GL;
+                fresh = false;
+            }
+        }
+        if (lane < uint32_t(a.k)) {
+            const bool empty = uint32_t(key) == SENT_IDX;
+            a.out_idx[int64_t(i) * a.k + lane] = empty ? -1 : int32_t(uint32_t(key));
+            if (a.out_d2) a.out_d2[int64_t(i) * a.k + lane] = empty ? __builtin_inff() : key_d2(key);
+        }
+    }
+}
+
+}  // namespace
+
+hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, int grid, hipStream_t st) {
+    if (grid <= 0) return hipSuccess;
+    WaveArgs a = {};
+    a.nodes = t->d_nodes;
+    a.boxes = static_cast<const float*>(t->d_boxes);
+    a.N = int32_t(t->N);
+    a.shape = group_shape(t->N);
+    a.queries = c.queries;
+    a.n = c.n;
+    a.k = c.k;
+    a.R2 = c.R2;
+    a.out_idx = c.out_idx;
+    a.out_d2 = c.out_d2;
+    const dim3 g(grid), b(64);
+    switch (t->dim) {
+        case 2: hipLaunchKernelGGL(knn_wave<2>, g, b, 0, st, a); break;
+        case 3: hipLaunchKernelGGL(knn_wave<3>, g, b, 0, st, a); break;
+        case 4: hipLaunchKernelGGL(knn_wave<4>, g, b, 0, st, a); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace kd
