@@ -28,6 +28,7 @@ SOURCES = [
     ("kd_api.cpp", True, []),
     ("kd_build_host.cpp", False, []),
     ("kd_traverse.hip", True, []),
+    ("kd_packet.hip", True, ["-mllvm", "-amdgpu-mfma-vgpr-form"]),
     ("kd_wave.hip", True, []),
     ("kd_sort.hip", True, []),
     # matrix-core results in ordinary VGPRs (the MLP kernels read every

@@ -248,8 +248,9 @@ size_t query_scratch_bytes(int64_t Q, int dim, bool sorted, bool learned, bool h
 // Writes the queries as traversal records (NodeRec<dim>[Q]) into sq, in
 // Morton order on the top sort_bits bits (0: caller order), and clears
 // zero[0..nzero) on the way.  ws holds sort_scratch_bytes(Q, dim) when sort_bits > 0.
+// tree_order: by the path from the root to the query's cell instead.
 kd_status reorder_queries(kd_tree t, const float* queries, int64_t Q, int sort_bits, void* ws, void* sq,
-                          uint32_t* zero, uint32_t nzero, hipStream_t st);
+                          uint32_t* zero, uint32_t nzero, hipStream_t st, bool tree_order = false);
 // A caller-provided device scratch region of `bytes` bytes that replaces the
 // per-stream buffer; a call whose scratch does not fit fails with KD_EINVAL
 // before any launch.  Calls given one records no timing events.
@@ -257,16 +258,40 @@ struct FixedScratch {
     void* ptr;
     size_t bytes;
 };
-// kNN with one wave per query (kd_wave.hip).
+// Packet kNN (kd_packet.hip): 64 sorted queries per wave.  Queries it leaves
+// unanswered are appended to fb_recs / fb_w0 (a record and an upper bound of
+// the k-th squared distance each) and counted in *fb_count (zero at launch).
+struct PacketCall {
+    const void* sq;  // NodeRec<dim>[Q], sorted
+    uint32_t Q;
+    int k;
+    float R2;
+    int32_t* out_idx;
+    float* out_d2;
+    int vec_store;
+    uint32_t* fb_count;
+    void* fb_recs;   // NodeRec<dim>[Q]
+    float* fb_w0;    // [Q]
+};
+hipError_t launch_knn_packet(kd_tree t, int K, const PacketCall& c, hipStream_t st);
+// The packet kernel takes the tree (coordinates of ordinary size, split
+// dimensions by level).
+bool packet_tree(kd_tree t);
+// kNN with one wave per query (kd_wave.hip): caller queries, or records, each
+// with an upper bound of its k-th squared distance or none; the number of
+// records may lie on the device (n: the waves to launch for them).
 struct WaveCall {
-    const float* queries;  // [n][dim]
+    const float* queries;   // [n][dim], or NULL
+    const void* recs;       // NodeRec<dim>[]
+    const float* w0;        // NULL: R2
     uint32_t n;
+    const uint32_t* n_dev;  // NULL: n
     int k;
     float R2;
     int32_t* out_idx;
     float* out_d2;
 };
-hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, int grid, hipStream_t st);
+hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, hipStream_t st);
 // Range queries (kd_traverse.hip): box = false, queries_or_boxes holds
 // float [Q][dim] points and R2 the squared radius; box = true, it holds float
 // [Q][2][dim] boxes.  Writes out_count[Q] and, for cap > 0, out_idx[Q][cap]

@@ -1555,16 +1555,44 @@ struct StageEvents {
 
 // Calls of at most this many queries go one wave per query: their time there
 // is the launch and one query's chain of group loads until the waves fill the
-// GPU (1.6 ns a query after that), while a lane-by-lane call costs the sort
-// (6 launches) and the longest lane's chain of node loads (80-900 us)
-// however few its queries.  Uniform points, lane by lane -> by wave, us:
-// 10K 3-D points, k = 8: 250 queries 156 -> 13, 65,536 183 -> 95, 262,144
-// 227 -> 344; 1M 3-D points, k = 32: 250 437 -> 25, 262,144 622 -> 841,
-// k = 64: 262,144 1706 -> 1392; 200K 4-D points, k = 8: 65,536 373 -> 168,
-// 262,144 494 -> 570; 200K 2-D points (short chains), k = 1: 65,536 76 -> 51,
-// 262,144 101 -> 189, k = 64: 65,536 386 -> 270, 262,144 892 -> 1029.
+// GPU (1 to 2.5 ns a query after that), while the other kernels cost the sort
+// (6 launches) and their longest chain of loads (80-900 us) however few the
+// queries.  Uniform points, lane by lane / packets / by wave, us: 10K 3-D
+// points, k = 8: 250 queries 156 / 310 / 13, 100,000 206 / 123 / 126, 300,000
+// 237 / 154 / 359; 1M 3-D points, k = 32: 100,000 575 / 1125 / 297, 300,000
+// 880 / 814 / 817; 200K 4-D points, k = 8: 100,000 394 / 479 / 224, 300,000
+// 548 / 492 / 618, k = 32: 300,000 1475 / 1159 / 1083; 200K 2-D points (short
+// chains), k = 8: 100,000 124 / 238 / 112, 300,000 147 / 157 / 327, k = 32:
+// 100,000 273 / 599 / 186.  On clustered points the line would lie higher (3-D
+// 1M, k = 8, 300,000: 1655 / 664 / 559); it follows the uniform ones.  Lists
+// over 32 have no packets: 1M points, 524,288 queries, lane by lane / by wave:
+// 3-D 2.73 / 2.20 ms, 4-D 5.88 / 3.05 ms, 2-D 1.45 / 1.45 ms.
 static int64_t wave_queries(int dim, int K) {
-    return (dim == 2 ? int64_t(1) << 16 : int64_t(1) << 17) * (K > 32 ? 2 : 1);
+    if (K > 32) return dim == 2 ? 262144 : INT64_MAX;
+    if (dim == 2) return K > 8 ? 131072 : 65536;
+    if (dim == 3) return K > 16 ? 262144 : 131072;
+    return K > 16 ? 327680 : 196608;
+}
+
+// Up to here a by-wave call takes the queries as they come; longer ones are
+// sorted along the tree first, so that waves at work together share nodes.
+constexpr int64_t WAVE_UNSORTED = 327680;
+
+// Longer calls go in packets of 64 neighbouring queries when these are not
+// sparse against the points: a packet visits the leaves around all its queries,
+// which pays while these share them.  3-D, k = 8, uniform / mixture, lane by
+// lane -> packets, ms: 1M points, 1M queries 0.67 -> 0.47 / 1.26 -> 0.68, 8M
+// points, 1M queries 1.33 -> 1.14 / 3.59 -> 1.39, 300K queries 0.53 -> 1.36 /
+// 1.49 -> 1.51; k = 1: 1M points, 300K queries 0.195 -> 0.190 / 0.53 -> 0.27,
+// 8M points, 1M queries 0.49 -> 0.74 / 0.91 -> 0.78; 4-D, k = 8: 1M points, 4M
+// queries 5.4 -> 2.4, 2M points, 300K queries 0.77 -> 0.83 / 1.85 -> 0.85.  In
+// 2-D a lane's walk is short and its neighbours' walks alike: 200K points, 1M
+// queries, k = 8 0.32 -> 0.26 / 0.40 -> 0.42, k = 32 1.04 -> 0.73 / 1.19 ->
+// 1.36; the lanes keep it.
+static bool use_packets(kd_tree t, int K, int64_t Q) {
+    if (t->dim == 2 || K > 32 || !packet_tree(t)) return false;
+    const int64_t sparse = t->dim == 3 && K > 1 && K <= 16 ? 8 : 4;
+    return Q >= t->N / sparse;
 }
 
 kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& plan, int32_t* out_idx,
@@ -1590,7 +1618,8 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
     kd_status s = KD_OK;
     // few queries: one wave each (no scratch, one launch)
     const bool plain = plan.plain && !visited && !learned;
-    if (plain && Q <= wave_queries(t->dim, plan.K)) {
+    const bool by_wave = plain && Q <= wave_queries(t->dim, plan.K);
+    if (by_wave && Q <= WAVE_UNSORTED) {
         hipEvent_t ev = nullptr;
         if (!fixed) {
             s = timing_begin(st, &ev);
@@ -1603,10 +1632,11 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
         wc.R2 = plan.R2;
         wc.out_idx = out_idx;
         wc.out_d2 = out_d2;
-        const hipError_t we = launch_knn_wave(t, wc, int(Q), st);
+        const hipError_t we = launch_knn_wave(t, wc, st);
         if (we != hipSuccess) return hip_error(we, "knn_wave launch");
         return timing_end(st, ev, "traverse");
     }
+    const bool packet = plain && !by_wave && use_packets(t, plan.K, Q);
     const size_t cursor_bytes = size_t(MAX_GROUPS) * CURSOR_STRIDE * 4;  // 256 KB
     const size_t head = cursor_bytes + 4096;
     const size_t sq_bytes = (size_t(Q) * rec_bytes(t->dim) + 255) & ~size_t(255);
@@ -1657,7 +1687,7 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
     s = tbegin(&evs);
     if (s != KD_OK) return s;
     hipError_t e = hipSuccess;
-    s = reorder_queries(t, queries, Q, plan.sort_bits, sort_ws, sq, counter1, n_counters, st);
+    s = reorder_queries(t, queries, Q, plan.sort_bits, sort_ws, sq, counter1, n_counters, st, packet || by_wave);
     if (s != KD_OK) return s;
     s = timing_end(st, evs, "sort");
     if (s != KD_OK) return s;
@@ -1710,6 +1740,44 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
         a.fb_count = fb_count;
         a.fb_flag = learned->fb_flag;
         a.vis_total = vis_total;
+    }
+    if (packet || by_wave) {
+        WaveCall wc = {};
+        wc.k = plan.k;
+        wc.R2 = plan.R2;
+        wc.out_idx = out_idx;
+        wc.out_d2 = out_d2;
+        hipEvent_t evp;
+        s = tbegin(&evp);
+        if (s != KD_OK) return s;
+        if (packet) {
+            // what the packets leave over is finished with one wave per
+            // query.  The sort's buffers are free by now and hold that list.
+            char* w = static_cast<char*>(sort_ws);
+            PacketCall pc = {};
+            pc.sq = sq;
+            pc.Q = uint32_t(Q);
+            pc.k = plan.k;
+            pc.R2 = plan.R2;
+            pc.out_idx = out_idx;
+            pc.out_d2 = out_d2;
+            pc.vec_store = a.vec_store;
+            pc.fb_count = fb_count;
+            pc.fb_recs = w;
+            pc.fb_w0 = reinterpret_cast<float*>(w + size_t(Q) * rec_bytes(t->dim));
+            e = launch_knn_packet(t, plan.K, pc, st);
+            if (e != hipSuccess) return hip_error(e, "knn_packet launch");
+            wc.recs = pc.fb_recs;
+            wc.w0 = pc.fb_w0;
+            wc.n = uint32_t(std::min<int64_t>(Q, int64_t(dev.cus) * 32));
+            wc.n_dev = fb_count;
+        } else {
+            wc.recs = sq;
+            wc.n = uint32_t(Q);
+        }
+        e = launch_knn_wave(t, wc, st);
+        if (e != hipSuccess) return hip_error(e, "knn_wave launch");
+        return timing_end(st, evp, "traverse");
     }
     const int coop_grid = dev.cus * 2;                      // workgroups of 4 waves
     const uint32_t heavy_cap = uint32_t(coop_grid) * 4u * KD_COOP_ROUNDS;  // rounds of one query per wave

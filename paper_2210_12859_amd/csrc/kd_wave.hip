@@ -1,9 +1,10 @@
 // kd_wave.hip -- kNN with one wave per query: the answer's latency instead of
 // its throughput.
 //
-// For calls with too few queries to fill the GPU with one lane each.  A
-// lane-by-lane walk is a chain of ~130 dependent node loads; here the wave's 64
-// lanes share the query:
+// For calls with too few queries to fill the GPU with one lane each, for lists
+// over 32 and for the queries the packet kernel leaves over.  A lane-by-lane
+// walk is a chain of ~130 dependent node loads; here the wave's 64 lanes share
+// the query:
 //   * groups of levels (kd_groups.h): lane l tests the bounding box of child
 //     group l % 32, so one load descends five levels;
 //   * 64 points at a time (two leaves, one in each half of the wave), one lane
@@ -24,6 +25,8 @@
 // 8: 156 us lane by lane (sort, walk, hand-off: 8 launches), 13 us here.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kd_groups.h"
 #include "kd_internal.h"
 #include "kd_list.h"
@@ -37,8 +40,11 @@ struct WaveArgs {
     const float* boxes;      // subtree boxes by node id
     int32_t N;
     GroupShape shape;
-    const float* queries;    // caller [n][D]
+    const float* queries;    // caller [n][D] (NULL: recs)
+    const void* recs;        // NodeRec<D>[]
+    const float* w0;         // with recs: upper bounds of the k-th squared distances (NULL: R2)
     uint32_t n;
+    const uint32_t* n_dev;   // number of recs, on the device (NULL: n)
     int k;
     float R2;
     int32_t* out_idx;
@@ -48,6 +54,10 @@ struct WaveArgs {
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t old, uint32_t v) {
     return uint32_t(__builtin_amdgcn_update_dpp(int(old), int(v), CTRL, 0xf, 0xf, false));
+}
+// The value of the lane below; 0 in lane 0 (wave_shr:1).
+__device__ __forceinline__ uint32_t shift_up(uint32_t v) {
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x138, 0xf, 0xf, true));
 }
 __device__ __forceinline__ uint32_t min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
@@ -75,17 +85,32 @@ __global__ __launch_bounds__(64) void knn_wave(WaveArgs a) {
     const int32_t slot_off = slot - (1 << slot_lv);
     const int32_t top_levels = a.shape.top_levels, leaf_group = a.shape.leaf_group;
     const bool six = a.shape.leaf_levels > GL;
+    const uint32_t n = a.n_dev ? *a.n_dev : a.n;
 
-    for (uint32_t i = blockIdx.x; i < a.n; i += gridDim.x) {
+    // workgroups of one XCD (blockIdx % 8) take neighbouring records
+    const uint32_t part = (n + 7u) >> 3;
+    for (uint32_t b = blockIdx.x; b < 8u * part; b += gridDim.x) {
+        const uint32_t i = a.queries ? b : (b & 7u) * part + (b >> 3);
+        if (i >= n) continue;
         float q[D];
+        uint32_t row = i;
+        float bound = a.R2;
+        if (a.queries) {
 #pragma unroll
-        for (int j = 0; j < D; ++j) q[j] = a.queries[size_t(i) * D + j];
+            for (int j = 0; j < D; ++j) q[j] = a.queries[size_t(i) * D + j];
+        } else {
+            const NodeRec<D>* r = reinterpret_cast<const NodeRec<D>*>(a.recs) + i;
+#pragma unroll
+            for (int j = 0; j < D; ++j) q[j] = r->c[j];
+            row = uint32_t(r->idx);
+            if (a.w0) bound = a.w0[i];
+        }
         bool ordered = true;  // no NaN
 #pragma unroll
         for (int j = 0; j < D; ++j) ordered = ordered & (q[j] == q[j]);
 
-        uint64_t key = make_key(a.R2, SENT_IDX);  // lane i: the i-th smallest
-        float worst = a.R2;                        // wave-uniform
+        uint64_t key = make_key(bound, SENT_IDX);  // lane i: the i-th smallest
+        float worst = bound;                       // wave-uniform
 
         // 64 points, one a lane; the candidates enter one by one
         auto take = [&](const int32_t r0, const int32_t lv0, const bool six0, const int32_t r1, const int32_t lv1,
@@ -110,15 +135,10 @@ __global__ __launch_bounds__(64) void knn_wave(WaveArgs a) {
                 cand &= cand - 1;
                 const uint64_t ck = (uint64_t(__builtin_amdgcn_readlane(__float_as_uint(d2), l)) << 32) |
                                     __builtin_amdgcn_readlane(uint32_t(idx), l);
-                // lanes before its place keep their key, the lane there takes
-                // it, the lanes behind take their neighbour's
-                const uint64_t below = wave_ballot(key < ck);
-                const uint32_t at = uint32_t(__popcll(below));
-                if (at >= uint32_t(a.k)) continue;
-                const uint32_t sh = dpp_u32<0x138>(0, uint32_t(key >> 32));  // wave_shr:1
-                const uint32_t sl = dpp_u32<0x138>(0, uint32_t(key));
-                const uint64_t moved = (uint64_t(sh) << 32) | sl;
-                key = lane < at ? key : (lane == at ? ck : moved);
+                // the sorted list of the lane helpers, one slot a lane: slot j
+                // becomes the candidate clamped to slots j - 1 and j
+                const uint64_t prev = (uint64_t(shift_up(uint32_t(key >> 32))) << 32) | shift_up(uint32_t(key));
+                key = key_max(prev, key_min(ck, key));
                 worst = __uint_as_float(__builtin_amdgcn_readlane(uint32_t(key >> 32), a.k - 1));
                 cand &= wave_ballot(d2 <= worst);
             }
@@ -194,28 +214,31 @@ __global__ __launch_bounds__(64) void knn_wave(WaveArgs a) {
         }
         if (lane < uint32_t(a.k)) {
             const bool empty = uint32_t(key) == SENT_IDX;
-            a.out_idx[int64_t(i) * a.k + lane] = empty ? -1 : int32_t(uint32_t(key));
-            if (a.out_d2) a.out_d2[int64_t(i) * a.k + lane] = empty ? __builtin_inff() : key_d2(key);
+            a.out_idx[int64_t(row) * a.k + lane] = empty ? -1 : int32_t(uint32_t(key));
+            if (a.out_d2) a.out_d2[int64_t(row) * a.k + lane] = empty ? __builtin_inff() : key_d2(key);
         }
     }
 }
 
 }  // namespace
 
-hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, int grid, hipStream_t st) {
-    if (grid <= 0) return hipSuccess;
+hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, hipStream_t st) {
+    if (c.n == 0) return hipSuccess;
     WaveArgs a = {};
     a.nodes = t->d_nodes;
     a.boxes = static_cast<const float*>(t->d_boxes);
     a.N = int32_t(t->N);
     a.shape = group_shape(t->N);
     a.queries = c.queries;
+    a.recs = c.recs;
+    a.w0 = c.w0;
     a.n = c.n;
+    a.n_dev = c.n_dev;
     a.k = c.k;
     a.R2 = c.R2;
     a.out_idx = c.out_idx;
     a.out_d2 = c.out_d2;
-    const dim3 g(grid), b(64);
+    const dim3 g(std::min<uint32_t>((c.n + 7u) / 8u * 8u, 1u << 22)), b(64);
     switch (t->dim) {
         case 2: hipLaunchKernelGGL(knn_wave<2>, g, b, 0, st, a); break;
         case 3: hipLaunchKernelGGL(knn_wave<3>, g, b, 0, st, a); break;
