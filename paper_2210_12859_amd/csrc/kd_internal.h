@@ -224,25 +224,29 @@ uint32_t batch_heavy_cap(int device);  // hand-off list entries of one class lau
 size_t sort_scratch_bytes(int64_t Q, int dim);
 // Stable LSD radix sort of n (key, value) pairs on key bits [0, bits), 8 bits
 // per pass, ping-ponging between (k0, v0) and (k1, v1); *in_second tells
-// which pair holds the result.  ws holds sort_pairs_scratch_bytes(n).
+// which pair holds the result.  lists such sorts at once, list i's arrays
+// i * stride elements behind the first's.  ws holds lists *
+// sort_pairs_scratch_bytes(n).
 size_t sort_pairs_scratch_bytes(uint32_t n);
 kd_status sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, uint32_t n, int bits, void* ws,
-                     hipStream_t st, bool* in_second);
+                     hipStream_t st, bool* in_second, int lists = 1, size_t stride = 0);
 // Canonical tree on the device (kd_build_gpu.hip): d_order[pos] = caller
-// index of the point at level-order position pos, for device points [N][dim].
-// d_pos_dims non-NULL: the widest-extent rule, each position's split
-// dimension written there (uint8 [N]); NULL: the dimension by level.
-kd_status build_level_order_device(const float* d_pts, int64_t N, int dim, int32_t* d_order, hipStream_t st,
-                                   uint8_t* d_pos_dims = nullptr);
+// index of the point at level-order position pos, for device points [N][dim];
+// a NaN or infinite coordinate sets *d_bad.  d_pos_dims non-NULL: the
+// widest-extent rule, each position's split dimension written there (uint8
+// [N]); NULL: the dimension by level.  ws holds build_scratch_bytes and is in
+// use until the stream has passed.
+size_t build_scratch_bytes(int64_t N, int dim, bool widest);
+kd_status build_level_order_device(const float* d_pts, int64_t N, int dim, int32_t* d_order, uint32_t* d_bad, void* ws,
+                                   hipStream_t st, uint8_t* d_pos_dims = nullptr);
 // Node records and subtree boxes from device points and order (kd_build_gpu.hip);
 // with stored dimensions (d_pos_dims by position) the records' ancestor splits
 // follow them and d_dims (uint8 [N + 2], by node id) receives the packed
-// dimensions of each node and its three nearest ancestors.
+// dimensions of each node and its three nearest ancestors.  root_box receives
+// the root's box_words(dim) words once more.
 kd_status pack_tree_device(const float* d_pts, const int32_t* d_order, int64_t N, int dim, void* d_nodes,
-                           float* d_boxes, hipStream_t st, const uint8_t* d_pos_dims = nullptr,
+                           float* d_boxes, float* root_box, hipStream_t st, const uint8_t* d_pos_dims = nullptr,
                            uint8_t* d_dims = nullptr);
-// *ok = no NaN or infinity among the N * dim device floats (synchronises).
-kd_status check_points_finite(const float* d_pts, int64_t N, int dim, hipStream_t st, bool* ok);
 // device scratch of one kd_knn-family call (kd_traverse.hip)
 size_t query_scratch_bytes(int64_t Q, int dim, bool sorted, bool learned, bool handoff);
 // Writes the queries as traversal records (NodeRec<dim>[Q]) into sq, in

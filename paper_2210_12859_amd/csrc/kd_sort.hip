@@ -114,6 +114,8 @@ struct SortPass {
     uint32_t ntiles;
     uint32_t* hist;
     uint32_t* totals;
+    size_t stride;      // pair sorts: elements from one list to the next (grid.y lists)
+    size_t hist_stride; // and words from one list's counts to the next's
     uint32_t* zero;   // cleared by radix_hist (nzero words), may be NULL
     uint32_t nzero;
     // tree order: the first pass's keys are the queries' paths from the root
@@ -200,20 +202,22 @@ __global__ __launch_bounds__(TILE_THREADS) void radix_hist(SortPass p) {
                 load_query<D>(p.m, i, c);
                 key = morton_code<D>(c, p.m.lo, p.m.scale);
             } else {
-                key = p.kin[i];
+                key = p.kin[D == 0 ? blockIdx.y * p.stride + i : i];
             }
             atomicAdd(&cnt[(key >> p.shift) & 0xffu], 1u);
         }
     }
     __syncthreads();
-    if (t < 256) p.hist[size_t(t) * p.ntiles + blockIdx.x] = cnt[t];
+    if (t < 256) p.hist[blockIdx.y * p.hist_stride + size_t(t) * p.ntiles + blockIdx.x] = cnt[t];
 }
 
 // One block per digit: exclusive scan of hist[digit][0..ntiles) in place;
 // totals[digit] = sum.
 __global__ __launch_bounds__(SCAN_THREADS) void radix_scan(uint32_t* __restrict__ hist, uint32_t ntiles,
-                                                           uint32_t* __restrict__ totals) {
+                                                           uint32_t* __restrict__ totals, size_t list_stride) {
     __shared__ uint32_t part[SCAN_THREADS];
+    hist += blockIdx.y * list_stride;
+    totals += blockIdx.y * list_stride;
     uint32_t* row = hist + size_t(blockIdx.x) * ntiles;
     const uint32_t per = (ntiles + SCAN_THREADS - 1) / SCAN_THREADS;
     const uint32_t b = threadIdx.x * per;
@@ -266,6 +270,9 @@ __global__ __launch_bounds__(TILE_THREADS) void radix_scatter(SortPass p) {
     __shared__ uint32_t sval[SORT_TILE];         // tile index of the key
     const uint32_t t = threadIdx.x;
     const uint32_t w = t >> 6;
+    const size_t list = D == 0 ? blockIdx.y * p.stride : 0;
+    p.hist += blockIdx.y * p.hist_stride;
+    p.totals += blockIdx.y * p.hist_stride;
     const uint32_t tile = blockIdx.x;
     const uint32_t tile0 = tile * uint32_t(SORT_TILE);
     const uint32_t tile_n = p.n - tile0 < uint32_t(SORT_TILE) ? p.n - tile0 : uint32_t(SORT_TILE);
@@ -308,7 +315,7 @@ __global__ __launch_bounds__(TILE_THREADS) void radix_scatter(SortPass p) {
                     key = morton_code<D>(c, p.m.lo, p.m.scale);
                 }
             } else {
-                key = p.kin[i];
+                key = p.kin[list + i];
             }
             d = (key >> p.shift) & 0xffu;
         }
@@ -356,8 +363,8 @@ __global__ __launch_bounds__(TILE_THREADS) void radix_scatter(SortPass p) {
         const uint32_t off = gbase[d] + (j - lstart[d]);
         if (off >= p.n) continue;  // never, as above
         if constexpr (D == 0) {
-            p.kout[off] = key;
-            p.vout[off] = p.vin[src];
+            p.kout[list + off] = key;
+            p.vout[list + off] = p.vin[list + src];
         } else {
             NodeRec<D> rec;
             if constexpr (FROM_Q) {
@@ -421,17 +428,18 @@ __global__ void batch_morton_codes(const BatchJob* __restrict__ jobs, int njobs,
 
 
 template <int D>
-hipError_t launch_pass(const SortPass& p, bool first, bool last, hipStream_t st) {
+hipError_t launch_pass(const SortPass& p, bool first, bool last, hipStream_t st, unsigned lists = 1) {
     const dim3 g(p.ntiles), b(TILE_THREADS), bs(SCAN_THREADS);
     if constexpr (D == 0) {
-        hipLaunchKernelGGL((radix_hist<0, false>), g, b, 0, st, p);
-        hipLaunchKernelGGL(radix_scan, dim3(256), bs, 0, st, p.hist, p.ntiles, p.totals);
-        hipLaunchKernelGGL((radix_scatter<0, false, false>), g, b, 0, st, p);
+        const dim3 gl(p.ntiles, lists);
+        hipLaunchKernelGGL((radix_hist<0, false>), gl, b, 0, st, p);
+        hipLaunchKernelGGL(radix_scan, dim3(256, lists), bs, 0, st, p.hist, p.ntiles, p.totals, p.hist_stride);
+        hipLaunchKernelGGL((radix_scatter<0, false, false>), gl, b, 0, st, p);
     } else {
         if (D > 2 && first && p.paths) hipLaunchKernelGGL((radix_hist<(D < 3 ? 3 : D), true, true>), g, b, 0, st, p);
         else if (first) hipLaunchKernelGGL((radix_hist<D, true>), g, b, 0, st, p);
         else hipLaunchKernelGGL((radix_hist<D, false>), g, b, 0, st, p);
-        hipLaunchKernelGGL(radix_scan, dim3(256), bs, 0, st, p.hist, p.ntiles, p.totals);
+        hipLaunchKernelGGL(radix_scan, dim3(256), bs, 0, st, p.hist, p.ntiles, p.totals, size_t(0));
         if (first && last) hipLaunchKernelGGL((radix_scatter<D, true, true>), g, b, 0, st, p);
         else if (first) hipLaunchKernelGGL((radix_scatter<D, true, false>), g, b, 0, st, p);
         else if (last) hipLaunchKernelGGL((radix_scatter<D, false, true>), g, b, 0, st, p);
@@ -487,12 +495,14 @@ size_t sort_pairs_scratch_bytes(uint32_t n) {
 }
 
 kd_status sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, uint32_t n, int bits, void* ws,
-                     hipStream_t st, bool* in_second) {
+                     hipStream_t st, bool* in_second, int lists, size_t stride) {
     *in_second = false;
     if (n <= 1 || bits <= 0) return KD_OK;
     SortPass p = {};
     p.n = n;
     p.ntiles = sort_tiles(n);
+    p.stride = stride;
+    p.hist_stride = sort_pairs_scratch_bytes(n) / sizeof(uint32_t);
     p.hist = static_cast<uint32_t*>(ws);
     p.totals = p.hist + size_t(256) * p.ntiles;
     const int passes = (bits + 7) / 8;
@@ -502,7 +512,7 @@ kd_status sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, uin
         p.vin = v0;
         p.kout = k1;
         p.vout = v1;
-        KD_HIP(launch_pass<0>(p, false, false, st));
+        KD_HIP(launch_pass<0>(p, false, false, st, unsigned(lists)));
         uint32_t* tk = k0; k0 = k1; k1 = tk;
         uint32_t* tv = v0; v0 = v1; v1 = tv;
         *in_second = !*in_second;
