@@ -263,8 +263,10 @@ kd_status kd_knn_noalloc(kd_tree t, const float* queries, int64_t Q, int k, floa
  * An empty tree gives counts 0.  A NaN query has no point in range.
  * Scratch: the per-stream workspace of the kd_knn family (query records and
  * sort buffers: at most kd_workspace_size(Q) for radius queries; box queries
- * add their centres, dim x 4 bytes per query); queries are taken in Morton
- * order.  Asynchronous on `stream`. */
+ * add their centres, dim x 4 bytes per query); queries are taken in a sorted
+ * order.  Long calls with dense queries and without `visited` or flags are
+ * answered 64 neighbouring queries to a wave, with the same results.
+ * Asynchronous on `stream`. */
 #define KD_RANGE_BOXES 1
 kd_status kd_radius_search(kd_tree t, const float* queries, int64_t Q, float maxRadius, int cap,
                            int32_t* out_idx, float* out_d2, uint32_t* out_count, uint32_t* visited,
@@ -280,7 +282,7 @@ kd_status kd_radius_search(kd_tree t, const float* queries, int64_t Q, float max
  *               smallest caller indices inside, ascending, -1 after the last.
  *   out_count : device uint32 [Q]: the number of points inside.
  *   visited, flags : as kd_radius_search.
- * Boxes are taken in the Morton order of their centres (the per-stream
+ * Boxes are taken in an order of their centres (the per-stream
  * workspace holds the centres too).  Asynchronous on `stream`. */
 kd_status kd_box_search(kd_tree t, const float* boxes, int64_t Q, int cap, int32_t* out_idx,
                         uint32_t* out_count, uint32_t* visited, int flags, kd_stream stream);

@@ -336,7 +336,9 @@ def kd_box_search(tree: Tree, lo, hi, cap=0, visited=None, flags=0, stream=None)
 def _range_all(call, Q, dev, capacity):
     import torch
     offsets = torch.empty(Q + 1, dtype=torch.int64, device=dev)
-    cap = int(capacity) if capacity is not None else max(1024, 16 * Q)
+    # a guess that most calls fit in (a second call counts again): 16 points a
+    # query, 64 while that stays under 256 MB
+    cap = int(capacity) if capacity is not None else max(1024, 16 * Q, min(64 * Q, 1 << 26))
     out = torch.empty(cap, dtype=torch.int32, device=dev)
     total = ctypes.c_int64()
     _check(call(offsets, out, cap, total))

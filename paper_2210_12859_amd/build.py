@@ -40,6 +40,7 @@ SOURCES = [
     ("kd_noalloc.hip", True, []),
     ("kd_build_gpu.hip", True, []),
     ("kd_range_all.hip", True, []),
+    ("kd_range_packet.hip", True, []),
 ]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math", "-Wall",

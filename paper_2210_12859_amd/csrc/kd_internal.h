@@ -296,6 +296,21 @@ struct WaveCall {
     float* out_d2;
 };
 hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, hipStream_t st);
+// Radius (boxes NULL) and box queries by packets (kd_range_packet.hip): counts,
+// and the cap best (cap > 0) or every point from fill_off on (fill_idx).
+struct RangePacketCall {
+    const void* recs;        // NodeRec<dim>[Q], sorted along the tree
+    const float* boxes;
+    uint32_t Q;
+    float R2;
+    int cap;
+    int32_t* out_idx;
+    float* out_d2;           // nullable
+    uint32_t* out_count;
+    const int64_t* fill_off;
+    int32_t* fill_idx;       // nullable
+};
+hipError_t launch_range_packet(kd_tree t, const RangePacketCall& c, hipStream_t st);
 // Range queries (kd_traverse.hip): box = false, queries_or_boxes holds
 // float [Q][dim] points and R2 the squared radius; box = true, it holds float
 // [Q][2][dim] boxes.  Writes out_count[Q] and, for cap > 0, out_idx[Q][cap]

@@ -2249,6 +2249,34 @@ hipError_t launch_range(int K, const RangeArgs& a, bool box, int grid, hipStream
 
 }  // namespace
 
+// Calls whose 64 neighbouring queries share most of what they reach go in
+// packets: by how dense the queries lie against the points, and enough of them
+// to fill the GPU.  Lane by lane / packets at mean 1, 8 and 48 points in range,
+// the worst of uniform and mixture data at and the worst below the line:
+//   2-D radius, and boxes without lists, from Q = 3/4 N: 1.05 (1/2 N: 0.96)
+//   3-D radius, from 1/2 N: 1.02 (1/8 N: 0.60)
+//   3-D boxes without lists, from 3/4 N and 150,000: 1.04 (100,000: 0.89); with
+//   lists, from N and 300,000: 1.03 (3/4 N: 0.90)
+//   4-D radius without lists, from N and 250,000: 1.02 (1/2 N: 0.92); with
+//   lists, from N and 500,000: 1.2 (300,000: 0.94)
+//   any other, from 2 N and 20,000: 1.1 (2-D boxes with lists and 4-D boxes at
+//   N: 0.75 and 0.93).
+// At 1M points and queries, mean 48 to 64, the gains are 1.2 to 2.5 (2-D), 2 to
+// 5.6 (3-D), 3.3 to 7 (4-D).  Lists over 32 keep the lanes (too many registers),
+// as do visit counts and explicit box tests, whose work is what is asked for.
+static bool range_packets(kd_tree t, int64_t Q, bool box, int cap, const uint32_t* visited, bool planes_only) {
+    if (visited || !planes_only || cap > 32 || Q < 20000) return false;
+    const int64_t N = t->N;
+    if (Q >= 2 * N) return true;
+    switch (t->dim) {
+        case 2: return !(box && cap > 0) && Q >= N - N / 4;
+        case 3:
+            if (!box) return Q >= N / 2;
+            return cap > 0 ? Q >= N && Q >= 300000 : Q >= N - N / 4 && Q >= 150000;
+        default: return !box && Q >= N && Q >= (cap > 0 ? 500000 : 250000);
+    }
+}
+
 kd_status run_range(kd_tree t, const float* queries_or_boxes, int64_t Q, bool box, float R2, int cap,
                     int32_t* out_idx, float* out_d2, uint32_t* out_count, uint32_t* visited, bool planes_only,
                     kd_stream stream, const int64_t* fill_off, int32_t* fill_idx) {
@@ -2283,7 +2311,9 @@ kd_status run_range(kd_tree t, const float* queries_or_boxes, int64_t Q, bool bo
     hipEvent_t evs;
     s = timing_begin(st, &evs);
     if (s != KD_OK) return s;
-    s = reorder_queries(t, keys, Q, sort_bits, base + head + sq_bytes, sq, counter, 64, st);
+    const bool packet = range_packets(t, Q, box, cap, visited, planes_only);
+    s = reorder_queries(t, keys, Q, sort_bits, base + head + sq_bytes, sq, counter, 64, st,
+                        packet && t->dim > 2 && !t->d_dims);
     if (s != KD_OK) return s;
     s = timing_end(st, evs, "sort");
     if (s != KD_OK) return s;
@@ -2303,6 +2333,25 @@ kd_status run_range(kd_tree t, const float* queries_or_boxes, int64_t Q, bool bo
     a.counter = counter;
     a.fill_off = fill_off;
     a.fill_idx = fill_idx;
+    if (packet) {
+        RangePacketCall pc = {};
+        pc.recs = sq;
+        pc.boxes = a.boxes;
+        pc.Q = a.Q;
+        pc.R2 = R2;
+        pc.cap = cap;
+        pc.out_idx = out_idx;
+        pc.out_d2 = out_d2;
+        pc.out_count = out_count;
+        pc.fill_off = fill_off;
+        pc.fill_idx = fill_idx;
+        hipEvent_t evp;
+        s = timing_begin(st, &evp);
+        if (s != KD_OK) return s;
+        const hipError_t ep = launch_range_packet(t, pc, st);
+        if (ep != hipSuccess) return hip_error(ep, "range packet launch");
+        return timing_end(st, evp, box ? "box" : "radius");
+    }
     const int K = cap > 0 ? k_template(cap) : 1;
     int64_t grid = int64_t(dev.cus) * 6;  // 24 waves per CU
     const int64_t need = (Q + 255) / 256;
