@@ -21,6 +21,7 @@
 #include <utility>
 #include <vector>
 
+#include "kd_groups.h"
 #include "kd_internal.h"
 
 struct kd_batch_s {
@@ -34,6 +35,11 @@ struct kd_batch_s {
         kd::MlpJob* d_mlp = nullptr;     // radius-model table of the class's jobs with a model
         int n_mlp = 0;
         uint32_t mlp_tiles = 0;
+        // at default options and without models: one wave per query, or the
+        // number of packets when every job's queries share enough (else 0)
+        bool by_wave = false;
+        uint32_t packets = 0;
+        bool other_kernels() const { return plan.plain && (by_wave || packets); }
         kd::QueryPlan plan;
         float est_ms = 0.0f;             // expected pipeline time: measured by the autotuner, else estimated
     };
@@ -147,10 +153,15 @@ kd_status enqueue_class(const kd_batch_s::Class& c, int device, hipStream_t st) 
     const ClassLayout L = class_layout(c, device);
     char* ws = static_cast<char*>(c.ws);
     const uint32_t* perm = nullptr;
-    kd_status s = batch_sort(c.d_jobs, c.njobs, c.dim, c.n, c.plan.sort_bits, ws, st, &perm);
-    if (s != KD_OK) return s;
     char* recs = ws + L.sort_b;
     uint32_t* counters = reinterpret_cast<uint32_t*>(recs + L.rec_b);
+    kd_status s = KD_OK;
+    if (!c.other_kernels() || !c.by_wave)
+        s = batch_sort(c.d_jobs, c.njobs, c.dim, c.n, c.plan.sort_bits, ws, st, &perm, c.other_kernels());
+    if (s != KD_OK) return s;
+    if (c.other_kernels())
+        return run_batch_packets(c.d_jobs, c.njobs, c.dim, c.K, c.n, c.by_wave ? 0 : c.packets, perm, recs, counters,
+                                 device, st);
     int32_t* heavy = reinterpret_cast<int32_t*>(recs + L.rec_b + L.cur_b);
     BatchLearned bl{c.d_mlp, c.n_mlp, c.mlp_tiles,
                     c.n_mlp ? reinterpret_cast<float*>(recs + L.rec_b + L.cur_b + L.heavy_b) : nullptr};
@@ -290,6 +301,7 @@ kd_status kd_batch_create(const kd_job* jobs, int n_jobs, kd_model model, const 
     // radius-model table of the 3-D jobs with a model
     std::map<std::pair<int, int>, std::vector<BatchJob>> groups;
     std::map<std::pair<int, int>, std::vector<MlpJob>> mlp;
+    std::map<std::pair<int, int>, bool> packet_jobs;  // every job of the class suits packets
     for (int i = 0; i < n_jobs; ++i) {
         const kd_job& J = jobs[i];
         b->total_queries += J.Q;
@@ -326,6 +338,10 @@ kd_status kd_batch_create(const kd_job* jobs, int n_jobs, kd_model model, const 
         bj.slot_base = uint32_t(start);
         bj.Q = uint32_t(J.Q);
         bj.vec_store = 0;
+        set_shape(bj, J.tree->N);
+        bj.packet_base = g.empty() ? 0 : g.back().packet_base + uint32_t((uint64_t(g.back().Q) + 63) / 64);
+        auto& all = packet_jobs.emplace(std::make_pair(D, K), true).first->second;
+        all = all && batch_packet_job(J.tree, K, J.Q);
         const kd_model m = J.model ? J.model : model;
         bj.learned = 0;
         if (m && D == 3) {
@@ -360,6 +376,12 @@ kd_status kd_batch_create(const kd_job* jobs, int n_jobs, kd_model model, const 
             c.plan.sort_bits = std::min(32, ((jb + 16 + 7) / 8) * 8);
         }
         c.est_ms = class_cost_estimate(c.dim, c.K, c.n);
+        if (mlp.find(kv.first) == mlp.end()) {
+            // the classes share the GPU, so the line is for their sum
+            c.by_wave = batch_by_wave(c.dim, c.K, b->total_queries);
+            const BatchJob& e = kv.second.back();
+            c.packets = packet_jobs[kv.first] ? e.packet_base + uint32_t((uint64_t(e.Q) + 63) / 64) : 0;
+        }
         b->classes.push_back(c);  // owned (freed on error) from here on
         kd_batch_s::Class& cc = b->classes.back();
         KD_HIP(hipMalloc(&cc.d_jobs, kv.second.size() * sizeof(BatchJob)));
@@ -448,14 +470,21 @@ kd_status kd_batch_autotune(kd_batch b, int reps, kd_stream stream, kd_opts* cla
         float best_ms = INFINITY;
         uint64_t ref = 0;
         bool have_ref = false;
-        for (int block : {256, 512}) {
+        // block 0: the class's plan as it is, where that takes other kernels
+        for (int block : {0, 256, 512}) {
             if (c.K >= 32 && block > 256) continue;
+            if (block == 0 && !(keep.plain && (c.by_wave || c.packets))) continue;
             for (int wpc : {16, 24, 32}) {
+                if (block == 0 && wpc > 16) break;
                 for (int bits : {16, 24, 32}) {
+                    if (block == 0 && bits > 16) break;
                     c.plan = keep;
-                    c.plan.block = block;
-                    c.plan.waves_per_cu = wpc;
-                    c.plan.sort_bits = bits;
+                    if (block) {
+                        c.plan.block = block;
+                        c.plan.waves_per_cu = wpc;
+                        c.plan.sort_bits = bits;
+                        c.plan.plain = false;
+                    }
                     s = enqueue_class(c, b->device, st);  // warm-up, and the outputs to check
                     uint64_t h = 0;
                     if (s == KD_OK) s = checksum(c, &h);
@@ -491,7 +520,7 @@ kd_status kd_batch_autotune(kd_batch b, int reps, kd_stream stream, kd_opts* cla
         *n_classes = int(b->classes.size());
         for (int i = 0; class_opts && i < cap && i < int(b->classes.size()); ++i) {
             const QueryPlan& p = b->classes[i].plan;
-            class_opts[i] = kd_opts{p.block, p.lds_levels, p.sort_bits, p.waves_per_cu,
+            class_opts[i] = kd_opts{p.plain ? 256 : p.block, p.lds_levels, p.sort_bits, p.waves_per_cu,
                                     p.heavy_default ? 0 : (p.heavy_trips > 0 ? p.heavy_trips : -1), p.prune};
         }
     }

@@ -39,6 +39,16 @@ inline GroupShape group_shape(int64_t N) {
     return s;
 }
 
+inline void set_shape(BatchJob& j, int64_t N) {
+    const GroupShape s = group_shape(N);
+    j.leaf_levels = s.leaf_levels;
+    j.top_levels = s.top_levels;
+    j.leaf_group = s.leaf_group;
+}
+__device__ __forceinline__ GroupShape job_shape(const BatchJob& j) {
+    return GroupShape{j.leaf_levels, j.top_levels, j.leaf_group};
+}
+
 template <int D>
 __device__ __forceinline__ void load_point(const TreeRec<D>* g1, const int32_t* ids, int32_t id, float (&p)[D],
                                            int32_t& idx) {

@@ -179,6 +179,8 @@ struct BatchJob {
     uint32_t Q;
     int32_t vec_store;
     int32_t learned;         // starts from the initial radius in worst0 (3-D jobs with a model)
+    uint32_t packet_base;    // first of the job's ceil(Q / 64) packets
+    int32_t leaf_levels, top_levels, leaf_group;  // GroupShape of the tree
 };
 
 // A batched job whose initial radii come from a radius model, as the MLP
@@ -210,13 +212,20 @@ struct LearnedSpec {
 };
 // Batched class pipeline (kd_sort.hip, kd_traverse.hip)
 size_t batch_sort_scratch_bytes(int64_t n);
+// tree_order: by the path from each job's root to the query's cell
 kd_status batch_sort(const BatchJob* d_jobs, int njobs, int dim, uint32_t n, int sort_bits, void* ws,
-                     hipStream_t st, const uint32_t** perm_out);
+                     hipStream_t st, const uint32_t** perm_out, bool tree_order);
 // learned (nullable): initial radii of the class's 3-D jobs with a model;
 // heavy_rows (nullable): [batch_heavy_cap][2] hand-off list (NULL: no hand-off)
 kd_status run_batch_class(const BatchJob* d_jobs, int njobs, int dim, int K, uint32_t n, const uint32_t* perm,
                           void* recs, uint32_t* counters, const QueryPlan& plan, int device, hipStream_t st,
                           const BatchLearned* learned, int32_t* heavy_rows);
+// The same class by packets (packets of all jobs) or, packets == 0, one wave per
+// query (perm unused); recs and counters as above.
+kd_status run_batch_packets(const BatchJob* d_jobs, int njobs, int dim, int K, uint32_t n, uint32_t packets,
+                            const uint32_t* perm, void* recs, uint32_t* counters, int device, hipStream_t st);
+bool batch_by_wave(int dim, int K, int64_t n);           // small classes: one wave per query
+bool batch_packet_job(kd_tree t, int K, int64_t Q);      // jobs whose queries share enough for packets
 size_t batch_rec_bytes();
 size_t batch_cursor_bytes();  // hand-off count and work cursors of one class launch
 uint32_t batch_heavy_cap(int device);  // hand-off list entries of one class launch
@@ -278,6 +287,18 @@ struct PacketCall {
     float* fb_w0;    // [Q]
 };
 hipError_t launch_knn_packet(kd_tree t, int K, const PacketCall& c, hipStream_t st);
+// The same for a class of jobs, n queries in `packets` packets; perm: class
+// slots in sorted order.  Left over: class slots and bounds.
+struct PacketJobs {
+    const BatchJob* jobs;
+    int njobs;
+    const uint32_t* perm;    // NULL: slot order
+    uint32_t n, packets;
+    uint32_t* fb_count;
+    uint32_t* fb_slot;
+    float* fb_w0;
+};
+hipError_t launch_knn_packet_jobs(int dim, int K, const PacketJobs& c, hipStream_t st);
 // The packet kernel takes the tree (coordinates of ordinary size, split
 // dimensions by level).
 bool packet_tree(kd_tree t);
@@ -296,6 +317,16 @@ struct WaveCall {
     float* out_d2;
 };
 hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, hipStream_t st);
+// The same for class slots of jobs (slots NULL: slots 0 .. n - 1).
+struct WaveJobs {
+    const BatchJob* jobs;
+    int njobs;
+    const uint32_t* slots;
+    const float* w0;        // NULL: the job's R2
+    uint32_t n;
+    const uint32_t* n_dev;  // NULL: n
+};
+hipError_t launch_knn_wave_jobs(int dim, const WaveJobs& c, hipStream_t st);
 // Radius (boxes NULL) and box queries by packets (kd_range_packet.hip): counts,
 // and the cap best (cap > 0) or every point from fill_off on (fill_idx).
 struct RangePacketCall {

@@ -74,8 +74,13 @@ struct PacketArgs {
     int vec_store;
     uint32_t leaf_limit;
     uint32_t* fb_count;      // queries left to the one-wave-per-query kernel
-    void* fb_recs;           // their records, NodeRec<D>[Q]
+    void* fb_recs;           // their records, NodeRec<D>[Q] (jobs: class slots)
     float* fb_w0;            // and upper bounds of their k-th squared distance
+    // jobs: what describes the tree and the outputs comes from the packet's job
+    const BatchJob* jobs;
+    int njobs;
+    uint32_t packets;
+    const uint32_t* perm;    // class slots in sorted order (NULL: slot order)
 };
 
 // Rounding of the matrix test.  A number is cut into two half-precision parts
@@ -240,25 +245,55 @@ __device__ __forceinline__ f32x16 products(const u32x4& a, const u32x4& b) {
 // a chunk.  Lists over 32 are left to the other kernels: the allocator would
 // copy live registers inside divergent regions, which loses them in the
 // inactive lanes.
-template <int D, int K>
+template <int D, int K, bool JOBS>
 __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 ? 4 : 5) : 1) void knn_packet(PacketArgs a) {
     __shared__ float4 pt[NPEND * 64];                    // points of the chunks held
     __shared__ int32_t pid[D == 4 ? NPEND * 64 : 1];     // their caller indices where w is a coordinate
     __shared__ uint8_t queue[(QCAP + 1) * 64];           // candidate i of lane l at 64 i + l
-    const TreeRec<D>* __restrict__ g1 = reinterpret_cast<const TreeRec<D>*>(a.nodes);
-    const int32_t* __restrict__ ids =
-        rec_has_idx(D) ? nullptr : reinterpret_cast<const int32_t*>(g1 + (int64_t(a.N) + 2));
     const uint32_t lane = __lane_id();
     // workgroups of one XCD (blockIdx % 8) take neighbouring packets
     const uint32_t pk = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    const uint32_t first = pk * 64u;
-    if (first >= a.Q) return;
+    uint32_t first = pk * 64u, end = a.Q;
+    uint32_t slot_base = 0;
+    const float* queries = nullptr;
+    if constexpr (JOBS) {
+        if (pk >= a.packets) return;
+        int lo = 0, hi = a.njobs - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (a.jobs[mid].packet_base <= pk) lo = mid;
+            else hi = mid - 1;
+        }
+        const BatchJob& J = a.jobs[lo];
+        a.nodes = J.nodes;
+        a.boxes = J.boxes;
+        a.N = J.N;
+        a.shape = job_shape(J);
+        a.k = J.k;
+        a.R2 = J.R2;
+        a.out_idx = J.out_idx;
+        a.out_d2 = J.out_d2;
+        a.vec_store = (J.k & 3) == 0 && ((reinterpret_cast<uintptr_t>(J.out_idx) | reinterpret_cast<uintptr_t>(J.out_d2)) & 15u) == 0;
+        queries = J.queries;
+        slot_base = J.slot_base;
+        first = J.slot_base + (pk - J.packet_base) * 64u;
+        end = J.slot_base + J.Q;
+    }
+    if (first >= end) return;
+    const TreeRec<D>* __restrict__ g1 = reinterpret_cast<const TreeRec<D>*>(a.nodes);
+    const int32_t* __restrict__ ids =
+        rec_has_idx(D) ? nullptr : reinterpret_cast<const int32_t*>(g1 + (int64_t(a.N) + 2));
     const uint32_t slot = first + lane;
-    const bool have = slot < a.Q;
+    const bool have = slot < end;
 
     Packet<D> s;
     int32_t row = 0;
-    {
+    if constexpr (JOBS) {
+        const uint32_t at = have ? slot : first;
+        row = int32_t((a.perm ? a.perm[at] : at) - slot_base);
+#pragma unroll
+        for (int j = 0; j < D; ++j) s.q[j] = queries[size_t(row) * D + j];
+    } else {
         const NodeRec<D>* r = reinterpret_cast<const NodeRec<D>*>(a.sq) + (have ? slot : first);
 #pragma unroll
         for (int j = 0; j < D; ++j) s.q[j] = r->c[j];
@@ -278,12 +313,16 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 ? 4 : 5) : 1) void k
         base = __builtin_amdgcn_readfirstlane(base);
         if (mine) {
             const uint32_t pos = base + __popcll(m & ((uint64_t(1) << lane) - 1));
-            NodeRec<D>* o = reinterpret_cast<NodeRec<D>*>(a.fb_recs) + pos;
-            NodeRec<D> rec;
+            if constexpr (JOBS) {
+                reinterpret_cast<uint32_t*>(a.fb_recs)[pos] = slot_base + uint32_t(row);
+            } else {
+                NodeRec<D>* o = reinterpret_cast<NodeRec<D>*>(a.fb_recs) + pos;
+                NodeRec<D> rec;
 #pragma unroll
-            for (int j = 0; j < D; ++j) rec.c[j] = s.q[j];
-            rec.idx = row;
-            *o = rec;
+                for (int j = 0; j < D; ++j) rec.c[j] = s.q[j];
+                rec.idx = row;
+                *o = rec;
+            }
             a.fb_w0[pos] = w0;
         }
     };
@@ -728,16 +767,17 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 ? 4 : 5) : 1) void k
     }
 }
 
-template <int D>
-hipError_t launch_packet_k(int K, const PacketArgs& a, int grid, hipStream_t st) {
-    const dim3 g(grid), b(64);
+template <int D, bool JOBS>
+hipError_t launch_packet_k(int K, const PacketArgs& a, int64_t packets, hipStream_t st) {
+    // a multiple of 8 workgroups, so that the XCDs' shares cover every packet
+    const dim3 g(unsigned((packets + 7) / 8 * 8)), b(64);
     switch (K) {
-        case 1: hipLaunchKernelGGL((knn_packet<D, 1>), g, b, 0, st, a); break;
-        case 2: hipLaunchKernelGGL((knn_packet<D, 2>), g, b, 0, st, a); break;
-        case 4: hipLaunchKernelGGL((knn_packet<D, 4>), g, b, 0, st, a); break;
-        case 8: hipLaunchKernelGGL((knn_packet<D, 8>), g, b, 0, st, a); break;
-        case 16: hipLaunchKernelGGL((knn_packet<D, 16>), g, b, 0, st, a); break;
-        case 32: hipLaunchKernelGGL((knn_packet<D, 32>), g, b, 0, st, a); break;
+        case 1: hipLaunchKernelGGL((knn_packet<D, 1, JOBS>), g, b, 0, st, a); break;
+        case 2: hipLaunchKernelGGL((knn_packet<D, 2, JOBS>), g, b, 0, st, a); break;
+        case 4: hipLaunchKernelGGL((knn_packet<D, 4, JOBS>), g, b, 0, st, a); break;
+        case 8: hipLaunchKernelGGL((knn_packet<D, 8, JOBS>), g, b, 0, st, a); break;
+        case 16: hipLaunchKernelGGL((knn_packet<D, 16, JOBS>), g, b, 0, st, a); break;
+        case 32: hipLaunchKernelGGL((knn_packet<D, 32, JOBS>), g, b, 0, st, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -781,11 +821,28 @@ hipError_t launch_knn_packet(kd_tree t, int K, const PacketCall& c, hipStream_t 
     a.fb_count = c.fb_count;
     a.fb_recs = c.fb_recs;
     a.fb_w0 = c.fb_w0;
-    // a multiple of 8 workgroups, so that the XCDs' shares cover every packet
-    const int grid = int(((c.Q + 63u) / 64u + 7u) / 8u * 8u);
+    const int64_t packets = (int64_t(c.Q) + 63) / 64;
     switch (t->dim) {
-        case 3: return launch_packet_k<3>(K, a, grid, st);
-        case 4: return launch_packet_k<4>(K, a, grid, st);
+        case 3: return launch_packet_k<3, false>(K, a, packets, st);
+        case 4: return launch_packet_k<4, false>(K, a, packets, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_knn_packet_jobs(int dim, int K, const PacketJobs& c, hipStream_t st) {
+    if (c.packets == 0) return hipSuccess;
+    PacketArgs a = {};
+    a.leaf_limit = packet_leaf_limit(dim, K, c.n);
+    a.fb_count = c.fb_count;
+    a.fb_recs = c.fb_slot;
+    a.fb_w0 = c.fb_w0;
+    a.jobs = c.jobs;
+    a.njobs = c.njobs;
+    a.packets = c.packets;
+    a.perm = c.perm;
+    switch (dim) {
+        case 3: return launch_packet_k<3, true>(K, a, c.packets, st);
+        case 4: return launch_packet_k<4, true>(K, a, c.packets, st);
     }
     return hipErrorInvalidValue;
 }

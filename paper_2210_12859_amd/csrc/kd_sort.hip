@@ -426,6 +426,32 @@ __global__ void batch_morton_codes(const BatchJob* __restrict__ jobs, int njobs,
     vals[i] = i;
 }
 
+// key = job index in the top jb bits, the path from the job's root below it
+// (as many levels as the tree has whole ones and `bits` holds)
+template <int D>
+__global__ void batch_path_codes(const BatchJob* __restrict__ jobs, int njobs, int jb, int bits, uint32_t n,
+                                 uint32_t* __restrict__ codes, uint32_t* __restrict__ vals) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int j = find_job(jobs, njobs, i);
+    const BatchJob& J = jobs[j];
+    const TreeRec<D>* g1 = static_cast<const TreeRec<D>*>(J.nodes);
+    const float* q = J.queries + size_t(i - J.slot_base) * D;
+    float c[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) c[d] = q[d];
+    const int whole = 31 - __clz(J.N);
+    const int levels = whole < bits ? whole : bits;
+    uint32_t id = 1;
+    for (int l = 0; l < levels; l += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (l + d < levels) id = (id << 1) | (c[d] - __uint_as_float(g1[id].w[d]) > 0.0f ? 1u : 0u);
+    }
+    const uint32_t path = levels ? (id - (1u << levels)) << (32 - levels) : 0u;
+    codes[i] = jb > 0 ? (uint32_t(j) << (32 - jb)) | (path >> jb) : path;
+    vals[i] = i;
+}
 
 template <int D>
 hipError_t launch_pass(const SortPass& p, bool first, bool last, hipStream_t st, unsigned lists = 1) {
@@ -456,7 +482,7 @@ size_t batch_sort_scratch_bytes(int64_t n) {
 }
 
 kd_status batch_sort(const BatchJob* d_jobs, int njobs, int dim, uint32_t n, int sort_bits, void* ws,
-                     hipStream_t st, const uint32_t** perm_out) {
+                     hipStream_t st, const uint32_t** perm_out, bool tree_order) {
     *perm_out = nullptr;
     if (n <= 1) return KD_OK;
     int jb = 0;
@@ -471,11 +497,17 @@ kd_status batch_sort(const BatchJob* d_jobs, int njobs, int dim, uint32_t n, int
     uint32_t* v1 = k1 + n;
     p.hist = v1 + n;
     p.totals = p.hist + size_t(256) * p.ntiles;
-    hipLaunchKernelGGL(batch_morton_codes, dim3((n + 255) / 256), dim3(256), 0, st, d_jobs, njobs, dim, jb, n, k0, v0);
-    KD_HIP(hipGetLastError());
     // the job bits must take part in the sort: sort on at least jb top bits
     int bits = sort_bits < jb ? ((jb + 7) / 8) * 8 : sort_bits;
     if (bits > 32) bits = 32;
+    const dim3 g((n + 255) / 256), b(256);
+    if (tree_order && dim == 3)
+        hipLaunchKernelGGL(batch_path_codes<3>, g, b, 0, st, d_jobs, njobs, jb, bits - jb, n, k0, v0);
+    else if (tree_order && dim == 4)
+        hipLaunchKernelGGL(batch_path_codes<4>, g, b, 0, st, d_jobs, njobs, jb, bits - jb, n, k0, v0);
+    else
+        hipLaunchKernelGGL(batch_morton_codes, g, b, 0, st, d_jobs, njobs, dim, jb, n, k0, v0);
+    KD_HIP(hipGetLastError());
     for (int q = 0; q < bits / 8; ++q) {
         p.shift = 32 - bits + 8 * q;
         p.kin = k0;

@@ -1595,6 +1595,42 @@ static bool use_packets(kd_tree t, int K, int64_t Q) {
     return Q >= t->N / sparse;
 }
 
+bool batch_by_wave(int dim, int K, int64_t n) { return n <= std::min(wave_queries(dim, K), WAVE_UNSORTED); }
+
+bool batch_packet_job(kd_tree t, int K, int64_t Q) { return use_packets(t, K, Q); }
+
+kd_status run_batch_packets(const BatchJob* d_jobs, int njobs, int dim, int K, uint32_t n, uint32_t packets,
+                            const uint32_t* perm, void* recs, uint32_t* counters, int device, hipStream_t st) {
+    if (n == 0) return KD_OK;
+    WaveJobs w = {};
+    w.jobs = d_jobs;
+    w.njobs = njobs;
+    w.n = n;
+    if (packets) {
+        hipLaunchKernelGGL(zero_u32, dim3(1), dim3(64), 0, st, counters, 1);
+        KD_HIP(hipGetLastError());
+        PacketJobs p = {};
+        p.jobs = d_jobs;
+        p.njobs = njobs;
+        p.perm = perm;
+        p.n = n;
+        p.packets = packets;
+        p.fb_count = counters;
+        // in the place of the lane kernel's records (32 bytes each)
+        p.fb_slot = static_cast<uint32_t*>(recs);
+        p.fb_w0 = static_cast<float*>(recs) + n;
+        const hipError_t e = launch_knn_packet_jobs(dim, K, p, st);
+        if (e != hipSuccess) return hip_error(e, "knn_packet launch (batched)");
+        w.slots = p.fb_slot;
+        w.w0 = p.fb_w0;
+        w.n = uint32_t(std::min<int64_t>(n, int64_t(device_info(device).cus) * 32));
+        w.n_dev = counters;
+    }
+    const hipError_t e = launch_knn_wave_jobs(dim, w, st);
+    if (e != hipSuccess) return hip_error(e, "knn_wave launch (batched)");
+    return KD_OK;
+}
+
 kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& plan, int32_t* out_idx,
                   float* out_d2, uint32_t* visited, kd_stream stream, const LearnedSpec* learned,
                   kd_stats* stats, const FixedScratch* fixed) {

@@ -49,6 +49,10 @@ struct WaveArgs {
     float R2;
     int32_t* out_idx;
     float* out_d2;
+    // jobs: what describes the tree and the outputs comes from the slot's job
+    const BatchJob* jobs;
+    int njobs;
+    const uint32_t* slots;   // class slots (NULL: 0 .. n - 1)
 };
 
 template <int CTRL>
@@ -71,20 +75,15 @@ __device__ __forceinline__ uint32_t min_low_half(uint32_t v) {
     return a < b ? a : b;
 }
 
-template <int D>
+template <int D, bool JOBS>
 __global__ __launch_bounds__(64) void knn_wave(WaveArgs a) {
     __shared__ float s_gap[MAX_GROUP_LEVELS][64];
-    const TreeRec<D>* __restrict__ g1 = reinterpret_cast<const TreeRec<D>*>(a.nodes);
-    const int32_t* __restrict__ ids =
-        rec_has_idx(D) ? nullptr : reinterpret_cast<const int32_t*>(g1 + (int64_t(a.N) + 2));
     const uint32_t lane = __lane_id();
     const bool upper = lane >= 32;
     // chunk slot of the lane (see kd_groups.h)
     const int32_t slot = int32_t(lane & 31u);
     const int32_t slot_lv = slot ? 31 - __builtin_clz(uint32_t(slot)) : 0;
     const int32_t slot_off = slot - (1 << slot_lv);
-    const int32_t top_levels = a.shape.top_levels, leaf_group = a.shape.leaf_group;
-    const bool six = a.shape.leaf_levels > GL;
     const uint32_t n = a.n_dev ? *a.n_dev : a.n;
 
     // workgroups of one XCD (blockIdx % 8) take neighbouring records
@@ -92,10 +91,39 @@ __global__ __launch_bounds__(64) void knn_wave(WaveArgs a) {
     for (uint32_t b = blockIdx.x; b < 8u * part; b += gridDim.x) {
         const uint32_t i = a.queries ? b : (b & 7u) * part + (b >> 3);
         if (i >= n) continue;
-        float q[D];
         uint32_t row = i;
+        if constexpr (JOBS) {
+            const uint32_t at = a.slots ? a.slots[i] : i;
+            int lo = 0, hi = a.njobs - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (a.jobs[mid].slot_base <= at) lo = mid;
+                else hi = mid - 1;
+            }
+            const BatchJob& J = a.jobs[lo];
+            a.nodes = J.nodes;
+            a.boxes = J.boxes;
+            a.N = J.N;
+            a.shape = job_shape(J);
+            a.k = J.k;
+            a.R2 = J.R2;
+            a.out_idx = J.out_idx;
+            a.out_d2 = J.out_d2;
+            a.recs = J.queries;
+            row = at - J.slot_base;
+        }
+        const TreeRec<D>* __restrict__ g1 = reinterpret_cast<const TreeRec<D>*>(a.nodes);
+        const int32_t* __restrict__ ids =
+            rec_has_idx(D) ? nullptr : reinterpret_cast<const int32_t*>(g1 + (int64_t(a.N) + 2));
+        const int32_t top_levels = a.shape.top_levels, leaf_group = a.shape.leaf_group;
+        const bool six = a.shape.leaf_levels > GL;
+        float q[D];
         float bound = a.R2;
-        if (a.queries) {
+        if constexpr (JOBS) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) q[j] = static_cast<const float*>(a.recs)[size_t(row) * D + j];
+            if (a.w0) bound = a.w0[i];
+        } else if (a.queries) {
 #pragma unroll
             for (int j = 0; j < D; ++j) q[j] = a.queries[size_t(i) * D + j];
         } else {
@@ -240,9 +268,28 @@ hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, hipStream_t st) {
     a.out_d2 = c.out_d2;
     const dim3 g(std::min<uint32_t>((c.n + 7u) / 8u * 8u, 1u << 22)), b(64);
     switch (t->dim) {
-        case 2: hipLaunchKernelGGL(knn_wave<2>, g, b, 0, st, a); break;
-        case 3: hipLaunchKernelGGL(knn_wave<3>, g, b, 0, st, a); break;
-        case 4: hipLaunchKernelGGL(knn_wave<4>, g, b, 0, st, a); break;
+        case 2: hipLaunchKernelGGL((knn_wave<2, false>), g, b, 0, st, a); break;
+        case 3: hipLaunchKernelGGL((knn_wave<3, false>), g, b, 0, st, a); break;
+        case 4: hipLaunchKernelGGL((knn_wave<4, false>), g, b, 0, st, a); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_knn_wave_jobs(int dim, const WaveJobs& c, hipStream_t st) {
+    if (c.n == 0) return hipSuccess;
+    WaveArgs a = {};
+    a.w0 = c.w0;
+    a.n = c.n;
+    a.n_dev = c.n_dev;
+    a.jobs = c.jobs;
+    a.njobs = c.njobs;
+    a.slots = c.slots;
+    const dim3 g(std::min<uint32_t>((c.n + 7u) / 8u * 8u, 1u << 22)), b(64);
+    switch (dim) {
+        case 2: hipLaunchKernelGGL((knn_wave<2, true>), g, b, 0, st, a); break;
+        case 3: hipLaunchKernelGGL((knn_wave<3, true>), g, b, 0, st, a); break;
+        case 4: hipLaunchKernelGGL((knn_wave<4, true>), g, b, 0, st, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
