@@ -276,6 +276,7 @@ struct FixedScratch {
 // the k-th squared distance each) and counted in *fb_count (zero at launch).
 struct PacketCall {
     const void* sq;  // NodeRec<dim>[Q], sorted
+    const float* w0; // initial squared radii by sorted place, or NULL
     uint32_t Q;
     int k;
     float R2;

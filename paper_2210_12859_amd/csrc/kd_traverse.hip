@@ -1653,8 +1653,11 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
     const bool handoff = heavy_trips > 0 && visited == nullptr;
     kd_status s = KD_OK;
     // few queries: one wave each (no scratch, one launch)
-    const bool plain = plan.plain && !visited && !learned;
-    const bool by_wave = plain && Q <= wave_queries(t->dim, plan.K);
+    // radii from a model suit packets as queries do, those of the caller may be
+    // anything (three times too large: lane by lane 0.52, packets 0.72 ms) and
+    // keep the lanes, as do counts of restarts
+    const bool plain = plan.plain && !visited && !stats && !(learned && !learned->params);
+    const bool by_wave = plain && !learned && Q <= wave_queries(t->dim, plan.K);
     if (by_wave && Q <= WAVE_UNSORTED) {
         hipEvent_t ev = nullptr;
         if (!fixed) {
@@ -1672,7 +1675,9 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
         if (we != hipSuccess) return hip_error(we, "knn_wave launch");
         return timing_end(st, ev, "traverse");
     }
-    const bool packet = plain && !by_wave && use_packets(t, plan.K, Q);
+    // without a first walk sparse queries cost more (2M points, 300,000 queries,
+    // k = 8: 0.34 lane by lane, 0.53 ms)
+    const bool packet = plain && !by_wave && use_packets(t, plan.K, Q) && (!learned || Q >= t->N / 2);
     const size_t cursor_bytes = size_t(MAX_GROUPS) * CURSOR_STRIDE * 4;  // 256 KB
     const size_t head = cursor_bytes + 4096;
     const size_t sq_bytes = (size_t(Q) * rec_bytes(t->dim) + 255) & ~size_t(255);
@@ -1739,7 +1744,7 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
         else
             e = launch_radius_to_worst0(t->dim, learned->r0, sq, uint32_t(Q), plan.R2, worst0, st);
         if (e != hipSuccess) return hip_error(e, "initial radius launch");
-        e = launch_learned_start(t->dim, t->d_nodes, int32_t(t->N), sq, worst0, uint32_t(Q), start, st);
+        if (!packet) e = launch_learned_start(t->dim, t->d_nodes, int32_t(t->N), sq, worst0, uint32_t(Q), start, st);
         if (e != hipSuccess) return hip_error(e, "start node launch");
         s = timing_end(st, evm, "mlp");
         if (s != KD_OK) return s;
@@ -1792,6 +1797,7 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
             char* w = static_cast<char*>(sort_ws);
             PacketCall pc = {};
             pc.sq = sq;
+            pc.w0 = worst0;
             pc.Q = uint32_t(Q);
             pc.k = plan.k;
             pc.R2 = plan.R2;

@@ -160,3 +160,24 @@ def test_widest_rule_and_streams():
     torch.cuda.synchronize()
     for i, d in got:
         assert torch.equal(i, want[0]) and torch.equal(d, want[1])
+
+
+@pytest.mark.parametrize("k,margin", [(1, 0.1), (8, 0.1), (8, 0.0), (8, -0.5), (8, 3.0), (5, 0.1), (20, 0.1)])
+def test_model_radii(k, margin):
+    """Model radii start the packets: good ones, ones too small (lists left short,
+    alone or many to a packet) and ones that reach too far."""
+    kd = _kd()
+    g = _gen(k)
+    P = torch.cat([torch.rand((150000, 3), generator=g, device="cuda:0"), _mixture(g, 150000, 3)])
+    Q = torch.cat([torch.rand((100001, 3), generator=g, device="cuda:0"), _mixture(g, 100000, 3)])
+    Q[::5003, 1] = math.nan
+    Q[1::5003] = math.inf
+    Q[2::5003] += 30.0
+    tree = kd.kd_build(P)
+    m = kd.kd_radius_model_train(tree, Q[3:20003:1][torch.isfinite(Q[3:20003]).all(dim=1)].contiguous(), k, epochs=2)
+    m = kd.kd_model_create(*m.params(), margin, k)
+    for r in (math.inf, 0.02):
+        print(f"[gpu] packets model k={k} margin={margin} r={r}", flush=True)
+        i, d = kd.kd_knn_learned(tree, m, Q, k, r)[:2]
+        ri, rd, _ = kd.kd_knn_ex(tree, Q, k, r, opts={"prune": 2})
+        assert torch.equal(i.view(ri.shape), ri) and torch.equal(d.view(rd.shape).view(torch.int32), rd.view(torch.int32))
