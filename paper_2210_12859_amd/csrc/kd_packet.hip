@@ -49,8 +49,12 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int NPEND = 4;        // pairs of chunks held in LDS until their candidates are inserted
-static_assert(NPEND * 64 <= 256, "a queue entry is a byte");
+// Pairs of chunks held in LDS until their candidates are inserted and the bounds
+// refreshed.  More fill the insertions better, fewer refresh sooner: 1M uniform /
+// mixture points, 4 -> 2, ms: k = 1 0.300 -> 0.301 / 0.453 -> 0.435, k = 8 0.465
+// -> 0.474 / 0.719 -> 0.687, k = 16 and 32 0.721 -> 0.707 / 2.146 -> 2.115.
+constexpr int pairs_held(int K) { return K == 8 ? 4 : 2; }
+static_assert(pairs_held(8) * 64 <= 256, "a queue entry is a byte");
 constexpr int QCAP = 16;        // candidates a query can hold until then
 constexpr uint32_t MAX_HOME = 8;          // chunk pairs of the first walk
 constexpr int SHORT_LISTS = 8;            // lists left short by initial radii that repeat a packet
@@ -252,6 +256,7 @@ __device__ __forceinline__ f32x16 products(const u32x4& a, const u32x4& b) {
 enum Source { CALL, RADII, JOBS };
 template <int D, int K, Source SRC>
 __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 : 5) : 1) void knn_packet(PacketArgs a) {
+    constexpr int NPEND = pairs_held(K);
     __shared__ float4 pt[NPEND * 64];                    // points of the chunks held
     __shared__ int32_t pid[D == 4 ? NPEND * 64 : 1];     // their caller indices where w is a coordinate
     __shared__ uint8_t queue[(QCAP + 1) * 64];           // candidate i of lane l at 64 i + l
@@ -538,6 +543,12 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 :
         // ---- first walk: an upper bound of every query's k-th distance
         if (bounded) {
             worst = a.R2;
+            // Short lists take one result for every 2 RUN points, the smallest: this
+            // loosens the bound little where few of the points are among the k
+            // nearest, and cannot tighten it.  fcp, 1M uniform / mixture points: 0.318
+            // -> 0.302 / 0.462 -> 0.451 ms with RUN 4 instead of 1; k = 8 with RUN 2:
+            // 0.472 -> 0.486, with 4: 0.585 ms.
+            constexpr int RUN = K <= 2 ? 4 : 1;
             float F[K];
 #pragma unroll
             for (int j = 0; j < K; ++j) F[j] = j < K - a.k ? -PT_NONE : PT_NONE;
@@ -566,12 +577,16 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 :
                 for (int c = 0; c < 2; ++c) {
                     const f32x16 acc_lo = products(pa[c], s.b_lo), acc_hi = products(pa[c], s.b_hi);
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        // both halves' results of the lane's own query; short
-                        // lists take only the smaller of the two, which can only
-                        // loosen the bound
-                        const u32x2 v = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc_lo[i]),
-                                                                         __float_as_uint(acc_hi[i]), false, false);
+                    for (int i = 0; i < 16; i += RUN) {
+                        float lo = acc_lo[i], hi = acc_hi[i];
+#pragma unroll
+                        for (int e = 1; e < RUN; ++e) {
+                            lo = fminf(lo, acc_lo[i + e]);
+                            hi = fminf(hi, acc_hi[i + e]);
+                        }
+                        // both halves' results of the lane's own query
+                        const u32x2 v = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi),
+                                                                         false, false);
                         if (K <= 8) {
                             insert(fminf(__uint_as_float(v.x), __uint_as_float(v.y)));
                         } else {
