@@ -339,7 +339,8 @@ struct RangePacketCall {
     int32_t* out_idx;
     float* out_d2;           // nullable
     uint32_t* out_count;
-    const int64_t* fill_off;
+    const int64_t* fill_off; // [Q + 1]
+    int64_t fill_cap;        // nothing is filled when fill_off[Q] is above it
     int32_t* fill_idx;       // nullable
 };
 hipError_t launch_range_packet(kd_tree t, const RangePacketCall& c, hipStream_t st);
@@ -350,10 +351,12 @@ hipError_t launch_range_packet(kd_tree t, const RangePacketCall& c, hipStream_t 
 // entered nodes) when given.  Q >= 1, N >= 1.  planes_only: no subtree box
 // tests (split planes only).  Fill mode (fill_idx non-NULL; cap 0 and
 // planes_only): every point in range of caller row r is also written to
-// fill_idx[fill_off[r] + its rank in traversal order].
+// fill_idx[fill_off[r] + its rank in traversal order], unless fill_off[Q] is
+// above fill_cap.  again: the stream's last call had the same queries.
 kd_status run_range(kd_tree t, const float* queries_or_boxes, int64_t Q, bool box, float R2, int cap,
                     int32_t* out_idx, float* out_d2, uint32_t* out_count, uint32_t* visited, bool planes_only,
-                    kd_stream stream, const int64_t* fill_off = nullptr, int32_t* fill_idx = nullptr);
+                    kd_stream stream, const int64_t* fill_off = nullptr, int32_t* fill_idx = nullptr,
+                    int64_t fill_cap = 0, bool again = false);
 kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& plan, int32_t* out_idx,
                   float* out_d2, uint32_t* visited, kd_stream stream, const LearnedSpec* learned = nullptr,
                   kd_stats* stats = nullptr, const FixedScratch* fixed = nullptr);

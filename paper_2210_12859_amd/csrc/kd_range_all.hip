@@ -7,7 +7,7 @@
 // subtree boxes on request, which may count whole subtrees), an exclusive
 // scan turns the counts into offsets, and the second writes each query's
 // points from its offset on, in the order the traversal reaches them (split
-// planes only, so every point in range is visited).  The scan is three
+// planes only, so every point in range is visited), if they all fit.  The scan is three
 // kernels: per-block scans of 4,096 counts, one workgroup scanning the block
 // totals, and a pass adding them.  Counts and totals sit in the stream's
 // second scratch buffer (kept by the library like the first).
@@ -154,15 +154,18 @@ kd_status range_all(kd_tree t, const float* in, int64_t Q, bool box, float maxRa
     KD_HIP(hipGetLastError());
     hipLaunchKernelGGL(scan_add, dim3(unsigned(nb)), dim3(SCAN_T), 0, st, offsets, Q, bs);
     KD_HIP(hipGetLastError());
+    // the same traversal again, writing each query's points from its offset; the
+    // kernels themselves see whether the total fits, so nothing waits for the
+    // host in between
+    if (capacity > 0) {
+        s = run_range(t, in, Q, box, R2, 0, nullptr, nullptr, cnt, nullptr, true, stream, offsets, out_idx, capacity,
+                      (flags & KD_RANGE_BOXES) == 0);
+        if (s != KD_OK) return s;
+    }
     int64_t tot = 0;
     KD_HIP(hipMemcpyAsync(&tot, offsets + Q, sizeof(tot), hipMemcpyDeviceToHost, st));
     KD_HIP(hipStreamSynchronize(st));
     *total = tot;
-    if (tot == 0 || tot > capacity) return KD_OK;
-    // the same traversal again, writing each query's points from its offset
-    s = run_range(t, in, Q, box, R2, 0, nullptr, nullptr, cnt, nullptr, true, stream, offsets, out_idx);
-    if (s != KD_OK) return s;
-    KD_HIP(hipStreamSynchronize(st));
     return KD_OK;
 }
 

@@ -61,6 +61,7 @@ struct RangePacketArgs {
     float* out_d2;
     uint32_t* out_count;
     const int64_t* fill_off;
+    int64_t fill_cap;
     int32_t* fill_idx;
 };
 
@@ -198,6 +199,7 @@ __global__ __launch_bounds__(64) void range_packet(RangePacketArgs a) {
     // workgroups of one XCD (blockIdx % 8) take neighbouring packets
     const uint32_t first = ((blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 64u;
     if (first >= a.Q) return;
+    if (MODE == FILL && a.fill_off[a.Q] > a.fill_cap) return;
     const bool have = first + lane < a.Q;
     const NodeRec<D> rec = reinterpret_cast<const NodeRec<D>*>(a.recs)[have ? first + lane : first];
     const int32_t row = rec.idx;
@@ -432,6 +434,7 @@ hipError_t launch_range_packet(kd_tree t, const RangePacketCall& c, hipStream_t 
     a.out_d2 = c.out_d2;
     a.out_count = c.out_count;
     a.fill_off = c.fill_off;
+    a.fill_cap = c.fill_cap;
     a.fill_idx = c.fill_idx;
     auto aligned = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     a.vec_store = c.cap % 4 == 0 && aligned(c.out_idx) && aligned(c.out_d2);

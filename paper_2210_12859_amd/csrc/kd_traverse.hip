@@ -1954,7 +1954,8 @@ struct RangeArgs {
     uint32_t* out_count;    // [Q]
     uint32_t* visited;      // [Q] entered nodes, or NULL
     uint32_t* counter;      // chunk cursor, zero at launch
-    const int64_t* fill_off;  // fill mode: first output slot of each caller row
+    const int64_t* fill_off;  // fill mode: first output slot of each caller row, then their number
+    int64_t fill_cap;         // nothing is filled when there are more
     int32_t* fill_idx;        // fill mode: every point in range, at fill_off[row] + its rank (NULL: off)
 };
 
@@ -2136,6 +2137,7 @@ __global__ __launch_bounds__(256) void range_persistent(RangeArgs a) {
     bool exhausted = false;
     RangeLane<D, K, Qy> s;
     s.curr = 0;
+    if (a.fill_idx && a.fill_off[a.Q] > a.fill_cap) return;
     for (;;) {
         const uint64_t need = wave_ballot(s.curr == 0);
         if (need && !exhausted) {
@@ -2321,7 +2323,7 @@ static bool range_packets(kd_tree t, int64_t Q, bool box, int cap, const uint32_
 
 kd_status run_range(kd_tree t, const float* queries_or_boxes, int64_t Q, bool box, float R2, int cap,
                     int32_t* out_idx, float* out_d2, uint32_t* out_count, uint32_t* visited, bool planes_only,
-                    kd_stream stream, const int64_t* fill_off, int32_t* fill_idx) {
+                    kd_stream stream, const int64_t* fill_off, int32_t* fill_idx, int64_t fill_cap, bool again) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const DeviceInfo& dev = device_info(t->device);
     const int sort_bits = 16;
@@ -2339,7 +2341,10 @@ kd_status run_range(kd_tree t, const float* queries_or_boxes, int64_t Q, bool bo
     void* sq = base + head;
     RangeArgs a = {};
     const float* keys = queries_or_boxes;
-    if (box) {
+    const bool packet = range_packets(t, Q, box, cap, visited, planes_only);
+    const bool sorted = again && packet;  // the call before left the same records
+    if (box) a.boxes = queries_or_boxes;
+    if (box && !sorted) {
         // boxes are ordered by their centres
         float* centres = reinterpret_cast<float*>(base + qb);
         const int64_t n = Q * t->dim;
@@ -2347,15 +2352,14 @@ kd_status run_range(kd_tree t, const float* queries_or_boxes, int64_t Q, bool bo
                            t->dim, centres);
         KD_HIP(hipGetLastError());
         keys = centres;
-        a.boxes = queries_or_boxes;
     }
     // Morton order (the first sort kernel clears the counter)
     hipEvent_t evs;
     s = timing_begin(st, &evs);
     if (s != KD_OK) return s;
-    const bool packet = range_packets(t, Q, box, cap, visited, planes_only);
-    s = reorder_queries(t, keys, Q, sort_bits, base + head + sq_bytes, sq, counter, 64, st,
-                        packet && t->dim > 2 && !t->d_dims);
+    if (!sorted)
+        s = reorder_queries(t, keys, Q, sort_bits, base + head + sq_bytes, sq, counter, 64, st,
+                            packet && t->dim > 2 && !t->d_dims);
     if (s != KD_OK) return s;
     s = timing_end(st, evs, "sort");
     if (s != KD_OK) return s;
@@ -2374,6 +2378,7 @@ kd_status run_range(kd_tree t, const float* queries_or_boxes, int64_t Q, bool bo
     a.visited = visited;
     a.counter = counter;
     a.fill_off = fill_off;
+    a.fill_cap = fill_cap;
     a.fill_idx = fill_idx;
     if (packet) {
         RangePacketCall pc = {};
@@ -2386,6 +2391,7 @@ kd_status run_range(kd_tree t, const float* queries_or_boxes, int64_t Q, bool bo
         pc.out_d2 = out_d2;
         pc.out_count = out_count;
         pc.fill_off = fill_off;
+        pc.fill_cap = fill_cap;
         pc.fill_idx = fill_idx;
         hipEvent_t evp;
         s = timing_begin(st, &evp);
