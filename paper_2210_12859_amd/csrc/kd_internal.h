@@ -327,7 +327,7 @@ struct WaveJobs {
     uint32_t n;
     const uint32_t* n_dev;  // NULL: n
 };
-hipError_t launch_knn_wave_jobs(int dim, const WaveJobs& c, hipStream_t st);
+hipError_t launch_knn_wave_jobs(int dim, int K, const WaveJobs& c, hipStream_t st);
 // Radius (boxes NULL) and box queries by packets (kd_range_packet.hip): counts,
 // and the cap best (cap > 0) or every point from fill_off on (fill_idx).
 struct RangePacketCall {

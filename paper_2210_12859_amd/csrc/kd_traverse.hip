@@ -1626,7 +1626,7 @@ kd_status run_batch_packets(const BatchJob* d_jobs, int njobs, int dim, int K, u
         w.n = uint32_t(std::min<int64_t>(n, int64_t(device_info(device).cus) * 32));
         w.n_dev = counters;
     }
-    const hipError_t e = launch_knn_wave_jobs(dim, w, st);
+    const hipError_t e = launch_knn_wave_jobs(dim, K, w, st);
     if (e != hipSuccess) return hip_error(e, "knn_wave launch (batched)");
     return KD_OK;
 }

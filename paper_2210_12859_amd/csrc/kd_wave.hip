@@ -12,7 +12,8 @@
 //     a vote for those that can enter the list;
 //   * the k-best list lies across the lanes (lane i: the i-th smallest
 //     (d2, index) key, so any k <= 64), an insertion is one shift of the lanes
-//     behind its place.
+//     behind its place; many candidates at once are sorted over the lanes and
+//     merged (bitonic networks of DPP exchanges).
 // Children are taken nearest first and again tested against the current k-th
 // distance; a group's own points come after its children, when the radius is
 // small.  Box distances are computed like point distances and rounding is
@@ -55,6 +56,17 @@ struct WaveArgs {
     const uint32_t* slots;   // class slots (NULL: 0 .. n - 1)
 };
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t NO_KEY = 0x7fe00000u;  // high word above every key's
+// Candidates of 64 points that enter the list together: one by one they cost
+// about 10 vector and 8 scalar instructions each, together 170.  In lists of 8
+// and more the first points of a query and most of what a long list meets are
+// that many.  150,001 2-D queries, k = 50: 0.377 -> 0.294 ms (from 12 on: 0.301,
+// from 8 on: 0.313), 1M 3-D queries, k = 50: 3.45 -> 2.59, 250,000, k = 32: 0.684
+// -> 0.560, 100,000, k = 8: 0.170 -> 0.166.
+constexpr int MANY = 20;
+constexpr int MERGE_K = 8;  // in shorter lists the test for it costs 8 %
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t old, uint32_t v) {
     return uint32_t(__builtin_amdgcn_update_dpp(int(old), int(v), CTRL, 0xf, 0xf, false));
@@ -75,7 +87,56 @@ __device__ __forceinline__ uint32_t min_low_half(uint32_t v) {
     return a < b ? a : b;
 }
 
-template <int D, bool JOBS>
+// The key of lane l ^ X (X = 1, 2, 3, 4, 7, 8, 15, 16, 31, 32, 63): DPP inside
+// rows of 16 lanes, row and half swaps beyond.
+template <int X>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+    if constexpr (X == 1) return dpp_u32<0xb1>(v, v);
+    else if constexpr (X == 2) return dpp_u32<0x4e>(v, v);
+    else if constexpr (X == 3) return dpp_u32<0x1b>(v, v);
+    else if constexpr (X == 7) return dpp_u32<0x141>(v, v);
+    else if constexpr (X == 15) return dpp_u32<0x140>(v, v);
+    else if constexpr (X == 8) return dpp_u32<0x128>(v, v);  // row_ror:8
+    else if constexpr (X == 4) return lane_xor<3>(lane_xor<7>(v));
+    else if constexpr (X == 16) {
+        // x: every even row twice, y: every odd one
+        const u32x2 s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (__lane_id() & 16u) ? s.x : s.y;
+    } else if constexpr (X == 32) {
+        const u32x2 s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return (__lane_id() & 32u) ? s.x : s.y;
+    } else if constexpr (X == 31) return lane_xor<16>(lane_xor<15>(v));
+    else return lane_xor<32>(lane_xor<31>(v));
+}
+template <int X>
+__device__ __forceinline__ uint64_t key_xor(uint64_t k) {
+    return (uint64_t(lane_xor<X>(uint32_t(k >> 32))) << 32) | lane_xor<X>(uint32_t(k));
+}
+// One exchange with lane l ^ X: the lane without bit B keeps the smaller key.
+template <int X, int B>
+__device__ __forceinline__ uint64_t exchange(uint64_t k) {
+    const uint64_t p = key_xor<X>(k);
+    const uint64_t lo = key_min(k, p), hi = key_max(k, p);
+    return (__lane_id() & uint32_t(B)) ? hi : lo;
+}
+// Ascending order of a bitonic sequence over the lanes of every group of 2 B.
+template <int B>
+__device__ __forceinline__ uint64_t bitonic(uint64_t k) {
+    k = exchange<B, B>(k);
+    if constexpr (B > 1) k = bitonic<B / 2>(k);
+    return k;
+}
+// Ascending order over the lanes of every group of 2 B, from any order: the
+// first exchange of a merge is with the mirrored lane.
+template <int B>
+__device__ __forceinline__ uint64_t sort_lanes(uint64_t k) {
+    if constexpr (B > 1) k = sort_lanes<B / 2>(k);
+    k = exchange<2 * B - 1, B>(k);
+    if constexpr (B > 1) k = bitonic<B / 2>(k);
+    return k;
+}
+
+template <int D, bool JOBS, bool MERGE>
 __global__ __launch_bounds__(64) void knn_wave(WaveArgs a) {
     __shared__ float s_gap[MAX_GROUP_LEVELS][64];
     const uint32_t lane = __lane_id();
@@ -158,6 +219,15 @@ __global__ __launch_bounds__(64) void knn_wave(WaveArgs a) {
                 d2 = d2 + dx * dx;
             }
             uint64_t cand = wave_ballot(ok & (d2 <= worst));
+            if (MERGE && __popcll(cand) >= MANY) {
+                // all at once: sorted over the lanes, the smaller of the list and
+                // the reversed candidates, and that bitonic sequence sorted
+                uint64_t c = (ok & (d2 <= worst)) ? make_key(d2, idx) : uint64_t(NO_KEY) << 32;
+                c = sort_lanes<32>(c);
+                key = bitonic<32>(key_min(key, key_xor<63>(c)));
+                worst = __uint_as_float(__builtin_amdgcn_readlane(uint32_t(key >> 32), a.k - 1));
+                cand = 0;
+            }
             while (cand) {
                 const int l = __builtin_ctzll(cand);
                 cand &= cand - 1;
@@ -248,6 +318,22 @@ __global__ __launch_bounds__(64) void knn_wave(WaveArgs a) {
     }
 }
 
+template <bool JOBS, bool MERGE>
+hipError_t launch_wave_m(int dim, const WaveArgs& a, int grid, hipStream_t st) {
+    const dim3 g(grid), b(64);
+    switch (dim) {
+        case 2: hipLaunchKernelGGL((knn_wave<2, JOBS, MERGE>), g, b, 0, st, a); break;
+        case 3: hipLaunchKernelGGL((knn_wave<3, JOBS, MERGE>), g, b, 0, st, a); break;
+        case 4: hipLaunchKernelGGL((knn_wave<4, JOBS, MERGE>), g, b, 0, st, a); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+template <bool JOBS>
+hipError_t launch_wave(int dim, bool merge, const WaveArgs& a, int grid, hipStream_t st) {
+    return merge ? launch_wave_m<JOBS, true>(dim, a, grid, st) : launch_wave_m<JOBS, false>(dim, a, grid, st);
+}
+
 }  // namespace
 
 hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, hipStream_t st) {
@@ -266,17 +352,11 @@ hipError_t launch_knn_wave(kd_tree t, const WaveCall& c, hipStream_t st) {
     a.R2 = c.R2;
     a.out_idx = c.out_idx;
     a.out_d2 = c.out_d2;
-    const dim3 g(std::min<uint32_t>((c.n + 7u) / 8u * 8u, 1u << 22)), b(64);
-    switch (t->dim) {
-        case 2: hipLaunchKernelGGL((knn_wave<2, false>), g, b, 0, st, a); break;
-        case 3: hipLaunchKernelGGL((knn_wave<3, false>), g, b, 0, st, a); break;
-        case 4: hipLaunchKernelGGL((knn_wave<4, false>), g, b, 0, st, a); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    const int g = int(std::min<uint32_t>((c.n + 7u) / 8u * 8u, 1u << 22));
+    return launch_wave<false>(t->dim, c.k >= MERGE_K, a, g, st);
 }
 
-hipError_t launch_knn_wave_jobs(int dim, const WaveJobs& c, hipStream_t st) {
+hipError_t launch_knn_wave_jobs(int dim, int K, const WaveJobs& c, hipStream_t st) {
     if (c.n == 0) return hipSuccess;
     WaveArgs a = {};
     a.w0 = c.w0;
@@ -285,14 +365,8 @@ hipError_t launch_knn_wave_jobs(int dim, const WaveJobs& c, hipStream_t st) {
     a.jobs = c.jobs;
     a.njobs = c.njobs;
     a.slots = c.slots;
-    const dim3 g(std::min<uint32_t>((c.n + 7u) / 8u * 8u, 1u << 22)), b(64);
-    switch (dim) {
-        case 2: hipLaunchKernelGGL((knn_wave<2, true>), g, b, 0, st, a); break;
-        case 3: hipLaunchKernelGGL((knn_wave<3, true>), g, b, 0, st, a); break;
-        case 4: hipLaunchKernelGGL((knn_wave<4, true>), g, b, 0, st, a); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    const int g = int(std::min<uint32_t>((c.n + 7u) / 8u * 8u, 1u << 22));
+    return launch_wave<true>(dim, K >= MERGE_K, a, g, st);
 }
 
 }  // namespace kd
