@@ -1555,23 +1555,27 @@ struct StageEvents {
 
 // Calls of at most this many queries go one wave per query: their time there
 // is the launch and one query's chain of group loads until the waves fill the
-// GPU (1 to 2.5 ns a query after that), while the other kernels cost the sort
-// (6 launches) and their longest chain of loads (80-900 us) however few the
-// queries.  Uniform points, lane by lane / packets / by wave, us: 10K 3-D
-// points, k = 8: 250 queries 156 / 310 / 13, 100,000 206 / 123 / 126, 300,000
-// 237 / 154 / 359; 1M 3-D points, k = 32: 100,000 575 / 1125 / 297, 300,000
-// 880 / 814 / 817; 200K 4-D points, k = 8: 100,000 394 / 479 / 224, 300,000
-// 548 / 492 / 618, k = 32: 300,000 1475 / 1159 / 1083; 200K 2-D points (short
-// chains), k = 8: 100,000 124 / 238 / 112, 300,000 147 / 157 / 327, k = 32:
-// 100,000 273 / 599 / 186.  On clustered points the line would lie higher (3-D
-// 1M, k = 8, 300,000: 1655 / 664 / 559); it follows the uniform ones.  Lists
-// over 32 have no packets: 1M points, 524,288 queries, lane by lane / by wave:
-// 3-D 2.73 / 2.20 ms, 4-D 5.88 / 3.05 ms, 2-D 1.45 / 1.45 ms.
+// GPU (1 to 5 ns a query after that), while the other kernels cost the sort (6
+// launches) and their longest chain of loads (80-900 us) however few the
+// queries.  Sorted kernels / by wave on 100,000 uniform points (on 1M points and
+// on clustered ones the ratios are higher), ms:
+//   2-D, k = 8: 65,536 queries 0.11 / 0.08, 131,072 0.12 / 0.15; k = 16: 65,536
+//   0.14 / 0.08, 131,072 0.15 / 0.16; k = 32: 131,072 0.23 / 0.20, 196,608 0.27 /
+//   0.29
+//   3-D, k = 8: 65,536 0.17 / 0.10, 131,072 0.17 / 0.20; k = 16: 131,072 0.23 /
+//   0.22, 196,608 0.25 / 0.32; k = 32: 196,608 0.43 / 0.42, 262,144 0.53 / 0.56
+//   (1M points: 0.81 / 0.59)
+//   4-D, k = 8: 131,072 0.31 / 0.28, 196,608 0.31 / 0.41; k = 16: 131,072 0.41 /
+//   0.34, 196,608 0.43 / 0.49; k = 32: 262,144 0.90 / 0.84, 393,216 1.03 / 1.45
+// Lists over 32 have no packets and lose to the lanes nowhere: 1M points and
+// queries, k = 64: 2-D 2.66 / 1.91, 3-D 5.07 / 2.94, 4-D 10.8 / 5.0 ms.
 static int64_t wave_queries(int dim, int K) {
-    if (K > 32) return dim == 2 ? 262144 : INT64_MAX;
-    if (dim == 2) return K > 8 ? 131072 : 65536;
-    if (dim == 3) return K > 16 ? 262144 : 131072;
-    return K > 16 ? 327680 : 196608;
+    if (K > 32) return INT64_MAX;
+    switch (dim) {
+        case 2: return K > 16 ? 131072 : (K > 8 ? 98304 : 65536);
+        case 3: return K > 16 ? 262144 : (K > 8 ? 131072 : 98304);
+        default: return K > 16 ? 262144 : (K > 8 ? 163840 : 131072);
+    }
 }
 
 // Up to here a by-wave call takes the queries as they come; longer ones are
@@ -1728,7 +1732,8 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
     s = tbegin(&evs);
     if (s != KD_OK) return s;
     hipError_t e = hipSuccess;
-    s = reorder_queries(t, queries, Q, plan.sort_bits, sort_ws, sq, counter1, n_counters, st, packet || by_wave);
+    s = reorder_queries(t, queries, Q, plan.sort_bits, sort_ws, sq, counter1, n_counters, st,
+                        (packet || by_wave) && t->dim > 2);
     if (s != KD_OK) return s;
     s = timing_end(st, evs, "sort");
     if (s != KD_OK) return s;

@@ -125,7 +125,7 @@ def test_line_of_the_route(dim, k, n, q):
     _check(P, torch.rand((q, dim), generator=g, device="cuda:0"), k, f"line D={dim} k={k} N={n} Q={q}")
 
 
-@pytest.mark.parametrize("dim", [3, 4])
+@pytest.mark.parametrize("dim", [2, 3, 4])
 @pytest.mark.parametrize("k", [33, 64])
 def test_long_lists_sorted(dim, k):
     """Lists over 32: the caller's order up to 327,680 queries, sorted above."""
