@@ -64,7 +64,10 @@ typedef enum {
 /* Launch tuning.  Every setting gives byte-identical results; only speed
  * differs.  Passing NULL means "the options kd_autotune chose for this tree
  * and k, else the built-in defaults"; in a struct, a field at its "default"
- * value below takes the built-in default. */
+ * value below takes the built-in default.  With every field at its default the
+ * library also chooses the kernel by the call's size: one wave per query for
+ * small calls and long lists, one wave for 64 neighbouring queries for long
+ * calls, else (and for any explicit option) the lane-by-lane traversal. */
 typedef struct {
     int block;       /* threads per workgroup: 256, 512 or 1024 (k > 16: 256); 64, 128
                         also accepted; 0 = default (256) */
@@ -477,8 +480,8 @@ kd_status kd_batch_info(kd_batch b, int* n_classes, int* class_dim, int* class_k
 
 /* --------------------------------------------------------------- autotune */
 
-/* Times the candidate launch options (workgroup size 256/512/1024 x waves
- * per CU 8..32 x Morton sort bits 0/16/24/32 x pruning rule x LDS levels
+/* Times the defaults and the candidate launch options (workgroup size
+ * 256/512/1024 x waves per CU 8..32 x Morton sort bits 0/16/24/32 x pruning rule x LDS levels
  * 0/10) on a sample of queries (device float32 [Qs][dim]) with the given k
  * and maxRadius, keeps the fastest on the tree for k's list size, and
  * returns it (best_out, best_ms are HOST and nullable).  Results never depend
