@@ -49,6 +49,10 @@ __device__ __forceinline__ uint64_t key_max(uint64_t a, uint64_t b) {
 // queries, k = 50: 0.885 -> 0.666 ms.
 template <int K>
 __device__ __forceinline__ void list_insert(uint64_t (&L)[K], uint64_t key) {
+    if constexpr (K == 1) {
+        L[0] = key < L[0] ? key : L[0];
+        return;
+    }
 #pragma unroll
     for (int j = K - 1; j > 0; --j) L[j] = key_max(L[j - 1], key_min(key, L[j]));
     L[0] = key_min(key, L[0]);

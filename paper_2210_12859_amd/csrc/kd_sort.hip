@@ -48,6 +48,8 @@ constexpr int SORT_TILE = TILE_THREADS * TILE_ROUNDS;  // keys per tile
 static_assert(TILE_THREADS >= 256 && TILE_THREADS <= 1024 && TILE_THREADS % 64 == 0, "tile threads");
 
 uint32_t sort_tiles(uint32_t n) { return (n + SORT_TILE - 1) / SORT_TILE; }
+// Words of one list's counts and totals.
+__host__ __device__ constexpr size_t list_words(uint32_t ntiles) { return 256 * size_t(ntiles) + 256 + 128; }
 
 __device__ __forceinline__ uint32_t spread_bits(uint32_t v, int D) {
     // insert D-1 zero bits between the low bits of v
@@ -100,10 +102,12 @@ __device__ __forceinline__ uint32_t morton_code(const float* c, const float* lo,
 // kout/vout.  D > 0: keys travel with NodeRec<D> records (coordinates +
 // caller row) kin/rin -> kout/rout; FROM_Q computes the keys and records from
 // the queries (row = slot), TO_REC writes only the records, to `rec`.
+// (Kept within 152 bytes: a longer argument costs every launch another line of
+// host memory, 0.3 us.)
 struct SortPass {
-    const uint32_t* kin;
+    const uint32_t* kin;  // tree order, first pass: the paths, written by radix_hist
     const uint32_t* vin;
-    const void* rin;
+    const void* rin;      // tree order, first pass: TreeRec<D>[N + 2]
     uint32_t* kout;
     uint32_t* vout;
     void* rout;
@@ -112,17 +116,13 @@ struct SortPass {
     uint32_t n;
     int shift;
     uint32_t ntiles;
+    uint32_t stride;  // pair sorts: elements from one list to the next (grid.y lists)
     uint32_t* hist;
     uint32_t* totals;
-    size_t stride;      // pair sorts: elements from one list to the next (grid.y lists)
-    size_t hist_stride; // and words from one list's counts to the next's
     uint32_t* zero;   // cleared by radix_hist (nzero words), may be NULL
     uint32_t nzero;
-    // tree order: the first pass's keys are the queries' paths from the root
-    const void* nodes;  // TreeRec<D>[N + 2]
-    int32_t N;
-    int levels;
-    uint32_t* paths;    // [n], written by the first radix_hist (NULL: Morton order)
+    int32_t N;        // tree order: points,
+    int levels;       // and levels of the paths (0: Morton codes)
 };
 
 template <int D>
@@ -132,16 +132,16 @@ __device__ __forceinline__ void load_query(const MortonArgs& m, uint32_t row, fl
 }
 
 // Paths of a thread's queries from the root, `levels` steps to the close child
-// (left: 0), at the top of the key (3-D and 4-D: 2-D calls sort by Morton code).  The order is the tree's own, so it is as
-// fine as the data is dense; the walks of a thread's queries go in step, so
-// their loads overlap.  Bound by the gathers (64 lines a load once the paths
+// (left: 0), at the top of the key (3-D and 4-D: 2-D calls sort by Morton
+// code).  The order is the tree's own, so it is as fine as the data is dense;
+// the walks of a thread's queries go in step, so their loads overlap.  Bound by the gathers (64 lines a load once the paths
 // part): the split coordinates of the first TOP_LEVELS levels are therefore
 // staged in LDS.  1M queries: 30 us from the nodes alone, 22 us here.
 constexpr int TOP_LEVELS = 12;  // a multiple of every D
 template <int D>
 __device__ __forceinline__ void tree_paths(const SortPass& p, uint32_t base, uint32_t (&key)[TILE_ROUNDS]) {
     __shared__ float top[1 << TOP_LEVELS];
-    const TreeRec<D>* g1 = static_cast<const TreeRec<D>*>(p.nodes);
+    const TreeRec<D>* g1 = static_cast<const TreeRec<D>*>(p.rin);
     const int staged = p.levels < TOP_LEVELS ? p.levels : TOP_LEVELS;
     float c[TILE_ROUNDS][D];
     int32_t id[TILE_ROUNDS];
@@ -196,19 +196,20 @@ __global__ __launch_bounds__(TILE_THREADS) void radix_hist(SortPass p) {
             uint32_t key;
             if constexpr (TREE) {
                 key = path[r];
-                p.paths[i] = key;
+                const_cast<uint32_t*>(p.kin)[i] = key;
             } else if constexpr (FROM_Q) {
                 float c[D > 0 ? D : 1];
                 load_query<D>(p.m, i, c);
                 key = morton_code<D>(c, p.m.lo, p.m.scale);
             } else {
-                key = p.kin[D == 0 ? blockIdx.y * p.stride + i : i];
+                key = p.kin[D == 0 ? size_t(blockIdx.y) * p.stride + i : i];
             }
             atomicAdd(&cnt[(key >> p.shift) & 0xffu], 1u);
         }
     }
     __syncthreads();
-    if (t < 256) p.hist[blockIdx.y * p.hist_stride + size_t(t) * p.ntiles + blockIdx.x] = cnt[t];
+    if constexpr (D == 0) p.hist += blockIdx.y * list_words(p.ntiles);
+    if (t < 256) p.hist[size_t(t) * p.ntiles + blockIdx.x] = cnt[t];
 }
 
 // One block per digit: exclusive scan of hist[digit][0..ntiles) in place;
@@ -270,9 +271,11 @@ __global__ __launch_bounds__(TILE_THREADS) void radix_scatter(SortPass p) {
     __shared__ uint32_t sval[SORT_TILE];         // tile index of the key
     const uint32_t t = threadIdx.x;
     const uint32_t w = t >> 6;
-    const size_t list = D == 0 ? blockIdx.y * p.stride : 0;
-    p.hist += blockIdx.y * p.hist_stride;
-    p.totals += blockIdx.y * p.hist_stride;
+    const size_t list = D == 0 ? size_t(blockIdx.y) * p.stride : 0;
+    if constexpr (D == 0) {
+        p.hist += blockIdx.y * list_words(p.ntiles);
+        p.totals += blockIdx.y * list_words(p.ntiles);
+    }
     const uint32_t tile = blockIdx.x;
     const uint32_t tile0 = tile * uint32_t(SORT_TILE);
     const uint32_t tile_n = p.n - tile0 < uint32_t(SORT_TILE) ? p.n - tile0 : uint32_t(SORT_TILE);
@@ -307,8 +310,8 @@ __global__ __launch_bounds__(TILE_THREADS) void radix_scatter(SortPass p) {
         if (valid) {
             const uint32_t i = tile0 + li;
             if constexpr (FROM_Q) {
-                if (p.paths) {
-                    key = p.paths[i];
+                if (p.levels) {
+                    key = p.kin[i];
                 } else {
                     float c[D > 0 ? D : 1];
                     load_query<D>(p.m, i, c);
@@ -459,10 +462,10 @@ hipError_t launch_pass(const SortPass& p, bool first, bool last, hipStream_t st,
     if constexpr (D == 0) {
         const dim3 gl(p.ntiles, lists);
         hipLaunchKernelGGL((radix_hist<0, false>), gl, b, 0, st, p);
-        hipLaunchKernelGGL(radix_scan, dim3(256, lists), bs, 0, st, p.hist, p.ntiles, p.totals, p.hist_stride);
+        hipLaunchKernelGGL(radix_scan, dim3(256, lists), bs, 0, st, p.hist, p.ntiles, p.totals, list_words(p.ntiles));
         hipLaunchKernelGGL((radix_scatter<0, false, false>), gl, b, 0, st, p);
     } else {
-        if (D > 2 && first && p.paths) hipLaunchKernelGGL((radix_hist<(D < 3 ? 3 : D), true, true>), g, b, 0, st, p);
+        if (D > 2 && first && p.levels) hipLaunchKernelGGL((radix_hist<(D < 3 ? 3 : D), true, true>), g, b, 0, st, p);
         else if (first) hipLaunchKernelGGL((radix_hist<D, true>), g, b, 0, st, p);
         else hipLaunchKernelGGL((radix_hist<D, false>), g, b, 0, st, p);
         hipLaunchKernelGGL(radix_scan, dim3(256), bs, 0, st, p.hist, p.ntiles, p.totals, size_t(0));
@@ -523,7 +526,7 @@ kd_status batch_sort(const BatchJob* d_jobs, int njobs, int dim, uint32_t n, int
 }
 
 size_t sort_pairs_scratch_bytes(uint32_t n) {
-    return (256 * size_t(sort_tiles(n)) + 256) * sizeof(uint32_t) + 512;
+    return list_words(sort_tiles(n)) * sizeof(uint32_t);
 }
 
 kd_status sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, uint32_t n, int bits, void* ws,
@@ -533,8 +536,7 @@ kd_status sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, uin
     SortPass p = {};
     p.n = n;
     p.ntiles = sort_tiles(n);
-    p.stride = stride;
-    p.hist_stride = sort_pairs_scratch_bytes(n) / sizeof(uint32_t);
+    p.stride = uint32_t(stride);
     p.hist = static_cast<uint32_t*>(ws);
     p.totals = p.hist + size_t(256) * p.ntiles;
     const int passes = (bits + 7) / 8;
@@ -607,15 +609,13 @@ kd_status reorder_queries(kd_tree t, const float* queries, int64_t Q, int sort_b
         q = q >= 23 ? q - 5 : std::min(q - 4, 16);
         p.levels = std::max(1, std::min(levels, q));
         sort_bits = (p.levels + 7) / 8 * 8;
-        p.nodes = t->d_nodes;
         p.N = int32_t(t->N);
-        p.paths = k0;
     }
     const int passes = sort_bits / 8;
     for (int q = 0; q < passes; ++q) {
         p.shift = 32 - sort_bits + 8 * q;
         p.kin = k0;
-        p.rin = r0;
+        p.rin = q == 0 && p.levels ? t->d_nodes : r0;
         p.kout = k1;
         p.rout = r1;
         const bool first = q == 0, last = q == passes - 1;
@@ -624,7 +624,6 @@ kd_status reorder_queries(kd_tree t, const float* queries, int64_t Q, int sort_b
         KD_HIP(e);
         p.zero = nullptr;
         p.nzero = 0;
-        p.paths = nullptr;
         uint32_t* tk = k0; k0 = k1; k1 = tk;
         void* tr = r0; r0 = r1; r1 = tr;
     }
