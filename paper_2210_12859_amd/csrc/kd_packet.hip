@@ -54,7 +54,17 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // mixture points, 4 -> 2, ms: k = 1 0.300 -> 0.301 / 0.453 -> 0.435, k = 8 0.465
 // -> 0.474 / 0.719 -> 0.687, k = 16 and 32 0.721 -> 0.707 / 2.146 -> 2.115.
 constexpr int pairs_held(int K) { return K == 8 ? 4 : 2; }
-static_assert(pairs_held(8) * 64 <= 256, "a queue entry is a byte");
+// Entry of the chunks held that a queue byte names.  Lanes without a candidate
+// read bytes that nothing wrote, so every byte has to name one of the entries.
+__host__ __device__ constexpr uint32_t held_entry(uint32_t byte, uint32_t entries) { return byte & (entries - 1u); }
+constexpr bool held_entries_hold(uint32_t entries) {
+    for (uint32_t b = 0; b < 256u; ++b)
+        if (held_entry(b, entries) >= entries || (b < entries && held_entry(b, entries) != b)) return false;
+    return entries <= 256u;  // a queue entry is a byte
+}
+static_assert(held_entries_hold(pairs_held(1) * 64) && held_entries_hold(pairs_held(8) * 64) &&
+                  held_entries_hold(pairs_held(32) * 64),
+              "queue bytes");
 constexpr int QCAP = 16;        // candidates a query can hold until then
 constexpr uint32_t MAX_HOME = 8;          // chunk pairs of the first walk
 constexpr int SHORT_LISTS = 8;            // lists left short by initial radii that repeat a packet
@@ -675,9 +685,10 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 :
         uint32_t npend = 0;  // chunks held
         auto insert_queue = [&]() {
             // every lane takes its next candidates, two at a time; lanes without
-            // one insert the largest key, which changes nothing
+            // one read some held point and insert the largest key, which changes
+            // nothing
             auto key_at = [&](uint32_t i) -> uint64_t {
-                const uint32_t at = queue[i * 64u + lane];
+                const uint32_t at = held_entry(queue[i * 64u + lane], NPEND * 64u);
                 const float4 w = pt[at];
                 float p[D];
                 p[0] = w.x;

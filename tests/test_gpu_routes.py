@@ -1,0 +1,58 @@
+"""Calls on both sides of the lines between the kNN kernels, against the oracle:
+one wave per query up to the line, packets of 64 sorted queries (or the lanes)
+above it.  The stage timers tell which kernels ran: only calls with one wave per
+query as they come have no sort."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# the longest call of one wave per query, by dimension and list size
+LINE = {(3, 8): 98304, (3, 16): 131072, (3, 32): 262144, (4, 8): 131072, (4, 16): 163840, (4, 32): 262144}
+
+
+def _data(rng, n, dim):
+    """Half uniform, half in narrow clusters: queries with few and with many
+    candidates share packets."""
+    mean = rng.random((32, dim), dtype=np.float32)
+    x = mean[rng.integers(0, 32, n)] + 0.003 * rng.standard_normal((n, dim)).astype(np.float32)
+    some = rng.random(n) < 0.5
+    x[some] = rng.random((int(some.sum()), dim), dtype=np.float32)
+    return np.ascontiguousarray(x, np.float32)
+
+
+def _call(kd, tree, Qs, k, r=np.inf):
+    """Rows and the number of sort stages of one call."""
+    q = torch.from_numpy(Qs).to("cuda:0")
+    kd.kd_timing_enable(True)
+    try:
+        for stage in ("sort", "traverse"):
+            kd.kd_timing_collect(stage)
+        i, d = kd.kd_knn(tree, q, k, r)
+        torch.cuda.synchronize()
+        sorts = kd.kd_timing_collect("sort")[1]
+        kd.kd_timing_collect("traverse")
+    finally:
+        kd.kd_timing_enable(False)
+    return i.cpu().numpy(), d.cpu().numpy(), sorts
+
+
+@pytest.mark.parametrize("dim", [3, 4])
+@pytest.mark.parametrize("k", [1, 2, 4, 7, 8, 16, 27])
+def test_packet_rows(oracle_lib, dim, k):
+    """Every list size of the packets, lanes without a candidate among them (the
+    bytes these read name no entry outside the chunks held)."""
+    import paper_2210_12859_amd as kd
+    rng = np.random.default_rng(dim * 64 + k)
+    q = LINE[(dim, 8 if k <= 8 else (16 if k <= 16 else 32))] + 77
+    P, Qs = _data(rng, 60000, dim), _data(rng, q, dim)
+    print(f"[gpu] packet rows D={dim} k={k} Q={q}", flush=True)
+    tree = kd.kd_build(torch.from_numpy(P).to("cuda:0"))
+    order = oracle_lib.build_tree(P)
+    for r in (np.inf, 0.02):
+        i, d, sorts = _call(kd, tree, Qs, k, r)
+        assert sorts == 1
+        ri, rd, _ = oracle_lib.knn(P, order, Qs, k, r)
+        assert np.array_equal(i.reshape(ri.shape), ri)
+        assert np.array_equal(d.reshape(rd.shape).view(np.uint32), rd.view(np.uint32))
