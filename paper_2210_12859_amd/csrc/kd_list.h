@@ -17,6 +17,14 @@ constexpr uint32_t SENT_IDX = 0x7fffffffu;  // index word of an empty list slot
 __device__ __forceinline__ uint64_t wave_ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
 
+// Between LDS writes of some lanes of a wave and reads of the same memory by
+// others.  The wave's LDS instructions are done in order, so this only holds the
+// compiler to that order; it costs no instruction.
+__device__ __forceinline__ void lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 __device__ __forceinline__ uint64_t make_key(float d2, int32_t idx) {
     return (uint64_t(__float_as_uint(d2)) << 32) | uint32_t(idx);
 }

@@ -714,6 +714,7 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 :
         };
         auto scan_chunks = [&](const Chunks& ch, bool last) {
             const uint32_t base = npend * 64u;
+            lds_order();  // other lanes read the entries held before
             {
                 const uint32_t at = base + (lane & 32u) + uint32_t(s.slot);
                 float4 w;
@@ -724,6 +725,7 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 :
                 pt[at] = w;
                 if (D == 4) pid[at] = ch.idx;
             }
+            lds_order();
             u32x4 pa[2];
             s.template point_operands<false>(ch.p, ch.ok, pa[0], pa[1]);
             uint32_t mask[2];

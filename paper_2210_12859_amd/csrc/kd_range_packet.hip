@@ -253,6 +253,7 @@ __global__ __launch_bounds__(64) void range_packet(RangePacketArgs a) {
     uint64_t m;          // items of the current group still to take
     uint64_t children;   // those of its items that are child groups
     auto enter = [&]() {
+        lds_order();  // other lanes read the items of the group here before
         const bool leaf = g == a.shape.leaf_group;
         const int32_t lv = g == 0 ? lvt : lv6, off = g == 0 ? offt : off6;
         children = leaf ? 0 : (g == 0 ? childt : child6);
@@ -303,6 +304,7 @@ __global__ __launch_bounds__(64) void range_packet(RangePacketArgs a) {
             }
             if (!wave_any(active & s.reaches(cl, ch, a.R2))) m &= ~(uint64_t(1) << j);
         }
+        lds_order();  // (not between the loads above: that cost 3 to 4 % of a call)
     };
     enter();
     for (;;) {
