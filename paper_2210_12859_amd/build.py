@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import concurrent.futures as cf
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -48,19 +49,53 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math", "
 DEVICE = ["--offload-arch=gfx950", "-fno-gpu-flush-denormals-to-zero", "-fno-gpu-rdc",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
+# Kernels that keep a value of the wave in its lanes (a stack, a list), some of
+# which a divergent block leaves inactive.  The register allocator may move such
+# a value inside such a block, which loses it there: seen with accumulator
+# registers (a walk that never ends), and spills are stored the same way.  A
+# build in which one of these kernels has either is refused.
+LANE_STATE = ("kd_packet.hip", "kd_range_packet.hip", "kd_wave.hip")
+RESOURCES = "-Rpass-analysis=kernel-resource-usage"
+
+
+def check_lane_state(remarks: str) -> int:
+    """Number of kernels in the compiler's resource remarks; raises for one with
+    accumulator registers or spilled vector registers."""
+    kernel, n = "", 0
+    for name, value in re.findall(r"remark: +(Function Name|AGPRs|VGPRs Spill): (\S+)", remarks):
+        if name == "Function Name":
+            kernel = value
+            n += 1
+        elif value != "0":
+            raise RuntimeError(f"{kernel}: {name} {value}; values kept in inactive lanes would be lost")
+    if n == 0:
+        raise RuntimeError("no resource remarks from the compiler")
+    return n
+
 
 def _compile(src: str, is_hip: bool, extra: list) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
     cmd = [HIPCC, *COMMON]
     if is_hip:
         cmd += ["-x", "hip", *DEVICE, *extra]
+        if src in LANE_STATE:
+            cmd += [RESOURCES]
     cmd += ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
-    if r.stderr.strip():
+    err = r.stderr
+    if src in LANE_STATE:
+        try:
+            check_lane_state(err)
+        except RuntimeError:
+            os.remove(obj)
+            raise
+        # each remark, the source line it quotes and the caret below
+        err = re.sub(r"^.*remark: .*\n(?: *\d* \|.*\n)*", "", err, flags=re.M)
+    if err.strip():
         # host-pass warnings about the packed-fp32 feature are expected
-        lines = [ln for ln in r.stderr.splitlines() if "packed-fp32-ops" not in ln]
+        lines = [ln for ln in err.splitlines() if "packed-fp32-ops" not in ln]
         if any(ln.strip() for ln in lines):
             sys.stderr.write("\n".join(lines) + "\n")
     return obj
