@@ -1732,8 +1732,10 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
     s = tbegin(&evs);
     if (s != KD_OK) return s;
     hipError_t e = hipSuccess;
+    // (the path order takes the split dimension from the level: trees that store
+    // it keep the Morton order)
     s = reorder_queries(t, queries, Q, plan.sort_bits, sort_ws, sq, counter1, n_counters, st,
-                        (packet || by_wave) && t->dim > 2);
+                        (packet || by_wave) && t->dim > 2 && !t->d_dims);
     if (s != KD_OK) return s;
     s = timing_end(st, evs, "sort");
     if (s != KD_OK) return s;
