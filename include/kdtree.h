@@ -64,10 +64,13 @@ typedef enum {
 /* Launch tuning.  Every setting gives byte-identical results; only speed
  * differs.  Passing NULL means "the options kd_autotune chose for this tree
  * and k, else the built-in defaults"; in a struct, a field at its "default"
- * value below takes the built-in default.  With every field at its default the
- * library also chooses the kernel by the call's size: one wave per query for
- * small calls and long lists, one wave for 64 neighbouring queries for long
- * calls, else (and for any explicit option) the lane-by-lane traversal. */
+ * value below takes the built-in default.  With every field at its default
+ * (block: 0 or 256) the library also chooses the kernel by the call's size: one
+ * wave per query for small calls and long lists, one wave for 64 neighbouring
+ * queries for long calls, else (and for any other option) the lane-by-lane
+ * traversal.  Options that kd_autotune chose apply to calls that go lane by
+ * lane; they take another call off its kernel only where it is like the sample
+ * (the same kernel, half to twice as many queries). */
 typedef struct {
     int block;       /* threads per workgroup: 256, 512 or 1024 (k > 16: 256); 64, 128
                         also accepted; 0 = default (256) */
@@ -486,12 +489,15 @@ kd_status kd_batch_info(kd_batch b, int* n_classes, int* class_dim, int* class_k
  * and maxRadius, keeps the fastest on the tree for k's list size, and
  * returns it (best_out, best_ms are HOST and nullable).  Results never depend
  * on the choice: every candidate's results are checked equal to the first's
- * (64-bit checksum of the result rows; a difference is KD_EHIP).
+ * (64-bit checksum of the result rows; a difference is KD_EHIP).  Where the
+ * defaults take another kernel than the lanes, the fastest options of the lanes
+ * are kept beside the winner, for calls that go lane by lane.
  * Synchronises the stream. */
 kd_status kd_autotune(kd_tree t, const float* sample_q, int64_t Qs, int k, float maxRadius, kd_opts* best_out,
                       float* best_ms, kd_stream stream);
 /* The options kept on the tree for k (KD_EINVAL if none), and setting them
- * (for example from a cache file). */
+ * (for example from a cache file); options set this way apply to calls that go
+ * lane by lane. */
 kd_status kd_tree_get_tuned(kd_tree t, int k, kd_opts* out);
 kd_status kd_tree_set_tuned(kd_tree t, int k, const kd_opts* opts);
 

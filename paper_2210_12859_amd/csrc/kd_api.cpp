@@ -249,16 +249,21 @@ __global__ void fill_zero_u32(uint32_t* p, int64_t n) {
     if (i < n) p[i] = 0;
 }
 
-kd_status resolve_plan(kd_tree t, int k, float maxRadius, const kd_opts* o, QueryPlan& p) {
+kd_status resolve_plan(kd_tree t, int k, float maxRadius, const kd_opts* o, int64_t Q, Route route, QueryPlan& p) {
     p.k = k;
     p.K = k_template(k);
     float r = maxRadius;
     p.R2 = r * r;  // binary32 product; +inf stays +inf
     kd_opts use{0, -1, -1, 0, 0, 0};
-    kd_opts tuned;
+    TuneEntry tuned;
     if (o) use = *o;
     else if (t && tuned_opts(t, p.K, &tuned)) {
-        use = tuned;
+        // Tuned options are the lanes'.  Calls that take another kernel keep it
+        // (250 queries, k = 8: 12 us by wave, 160 by lane; 1M: 0.46 ms in packets,
+        // 0.69), unless the sample took the same one, the lanes beat it there, and
+        // the call is of about the sample's size, where that measurement holds.
+        if (route == Route::lanes) use = tuned.lanes;
+        else if (route == tuned.route && Q <= 2 * tuned.sample && tuned.sample <= 2 * Q) use = tuned.opts;
         // a tuned box rule is the default rule, which still gives the
         // paper's count when visited is requested
         if (use.prune == 2) use.prune = 0;
@@ -325,8 +330,9 @@ kd_status read_back(kd_tree_s* t, const int32_t* d_order, size_t count, const ui
 
 }  // namespace
 
-kd_status resolve_plan_public(kd_tree t, int k, float maxRadius, const kd_opts* o, QueryPlan& p) {
-    return resolve_plan(t, k, maxRadius, o, p);
+kd_status resolve_plan_public(kd_tree t, int k, float maxRadius, const kd_opts* o, int64_t Q, Route route,
+                              QueryPlan& p) {
+    return resolve_plan(t, k, maxRadius, o, Q, route, p);
 }
 
 kd_status check_query_args_public(kd_tree t, const float* queries, int64_t Q, int k, float maxRadius,
@@ -340,7 +346,7 @@ kd_status knn_entry(kd_tree t, const float* queries, int64_t Q, int k, float max
     kd_status s = check_query_args(t, queries, Q, k, maxRadius, out_idx, fn);
     if (s != KD_OK) return s;
     QueryPlan plan;
-    s = resolve_plan(t, k, maxRadius, opts, plan);
+    s = resolve_plan(t, k, maxRadius, opts, Q, call_route(t, k_template(k), Q, visited != nullptr, false), plan);
     if (s != KD_OK) return s;
     if (Q == 0) return KD_OK;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);

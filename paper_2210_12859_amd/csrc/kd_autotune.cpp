@@ -5,7 +5,8 @@
 // which lane serves which query and in what order), so the choice is purely
 // a matter of speed.  The winner is kept on the tree per compiled list size
 // K and used by kd_knn / kd_knn_ex / kd_knn_learned when called with default
-// options.
+// options: by calls that go lane by lane, and by calls like the sample (see
+// resolve_plan in kd_api.cpp).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -16,24 +17,24 @@
 
 namespace kd {
 
-bool tuned_opts(kd_tree t, int K, kd_opts* out) {
+bool tuned_opts(kd_tree t, int K, TuneEntry* out) {
     std::lock_guard<std::mutex> lk(t->tune_mu);
     for (const auto& e : t->tuned)
         if (e.k_template == K) {
-            *out = e.opts;
+            *out = e;
             return true;
         }
     return false;
 }
 
-void set_tuned(kd_tree t, int K, const kd_opts& o) {
+void set_tuned(kd_tree t, const TuneEntry& n) {
     std::lock_guard<std::mutex> lk(t->tune_mu);
     for (auto& e : t->tuned)
-        if (e.k_template == K) {
-            e.opts = o;
+        if (e.k_template == n.k_template) {
+            e = n;
             return;
         }
-    t->tuned.push_back(TuneEntry{K, o});
+    t->tuned.push_back(n);
 }
 
 }  // namespace kd
@@ -88,8 +89,9 @@ kd_status kd_autotune(kd_tree t, const float* sample_q, int64_t Qs, int k, float
         cleanup();
         return hip_error(e, "kd_autotune: setup");
     }
-    float best = INFINITY;
-    kd_opts bo = cands.front();
+    float best = INFINITY, best_lanes = INFINITY;
+    kd_opts bo = cands.front(), bl = cands.front();
+    const Route route = call_route(t, K, Qs, false, false);
     uint64_t ref = 0;
     bool have_ref = false;
     for (const kd_opts& o : cands) {
@@ -131,9 +133,14 @@ kd_status kd_autotune(kd_tree t, const float* sample_q, int64_t Qs, int k, float
             best = ms;
             bo = o;
         }
+        // the defaults count as the lanes' where they take these
+        if (ms < best_lanes && (route == Route::lanes || &o != &cands.front())) {
+            best_lanes = ms;
+            bl = o;
+        }
     }
     cleanup();
-    set_tuned(t, K, bo);
+    set_tuned(t, TuneEntry{K, bo, bl, route, Qs});
     if (best_out) *best_out = bo;
     if (best_ms) *best_ms = best;
     return KD_OK;
@@ -142,7 +149,9 @@ kd_status kd_autotune(kd_tree t, const float* sample_q, int64_t Qs, int k, float
 kd_status kd_tree_get_tuned(kd_tree t, int k, kd_opts* out) {
     if (!t || !out) return set_error(KD_EINVAL, "kd_tree_get_tuned: NULL argument");
     if (k < 1 || k > KD_MAX_K) return set_error(KD_EINVAL, "kd_tree_get_tuned: k out of range [1, 64]");
-    if (!tuned_opts(t, k_template(k), out)) return set_error(KD_EINVAL, "kd_tree_get_tuned: not tuned for this k");
+    TuneEntry e;
+    if (!tuned_opts(t, k_template(k), &e)) return set_error(KD_EINVAL, "kd_tree_get_tuned: not tuned for this k");
+    *out = e.opts;
     return KD_OK;
 }
 
@@ -150,9 +159,9 @@ kd_status kd_tree_set_tuned(kd_tree t, int k, const kd_opts* o) {
     if (!t || !o) return set_error(KD_EINVAL, "kd_tree_set_tuned: NULL argument");
     if (k < 1 || k > KD_MAX_K) return set_error(KD_EINVAL, "kd_tree_set_tuned: k out of range [1, 64]");
     QueryPlan p;
-    kd_status s = resolve_plan_public(t, k, INFINITY, o, p);
+    kd_status s = resolve_plan_public(t, k, INFINITY, o, 0, Route::lanes, p);
     if (s != KD_OK) return s;
-    set_tuned(t, k_template(k), *o);
+    set_tuned(t, TuneEntry{k_template(k), *o, *o, Route::lanes, 0});
     return KD_OK;
 }
 

@@ -292,7 +292,7 @@ kd_status kd_batch_create(const kd_job* jobs, int n_jobs, kd_model model, const 
     // options shared by every class; the list size of each class sets its
     // default persistent grid
     QueryPlan base;
-    kd_status s = resolve_plan_public(nullptr, 1, INFINITY, opts, base);
+    kd_status s = resolve_plan_public(nullptr, 1, INFINITY, opts, 0, Route::lanes, base);
     if (s != KD_OK) return s;
     std::unique_ptr<kd_batch_s, void (*)(kd_batch)> b(new kd_batch_s, free_batch);
     KD_HIP(hipGetDevice(&b->device));

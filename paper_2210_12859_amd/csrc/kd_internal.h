@@ -74,10 +74,17 @@ inline int32_t box_id_limit(int64_t N) {
     return e <= 0 ? 1 : int32_t(1) << e;  // N < 2^30: e <= 28
 }
 
+// Kernels that a call at default options takes: lane by lane, one wave per
+// query, or packets.
+enum class Route { lanes, wave, packets };
+
 // Tuned launch parameters kept with a tree (filled by kd_autotune).
 struct TuneEntry {
     int k_template;  // compiled list size
-    kd_opts opts;
+    kd_opts opts;    // the fastest on the sample
+    kd_opts lanes;   // the fastest that the lanes take
+    Route route;     // the sample's at default options,
+    int64_t sample;  // and its queries (0: options set by the caller)
 };
 
 struct Workspace;
@@ -121,7 +128,7 @@ int64_t left_subtree_size(int64_t n);
 void build_level_order(const float* pts, int64_t N, int dim, int32_t* order, int threads);
 
 // ---- tuned options (kd_autotune.cpp) ----------------------------------------
-bool tuned_opts(kd_tree t, int K, kd_opts* out);
+bool tuned_opts(kd_tree t, int K, TuneEntry* out);
 
 // ---- device info --------------------------------------------------------
 struct DeviceInfo {
@@ -161,6 +168,10 @@ struct QueryPlan {
     bool plain = false;   // every option at its default: the call's kernel follows from its size
 };
 int k_template(int k);
+// The route of a kNN call (kd_traverse.hip).  lanes_only: it asks for what the
+// lanes alone give (visited nodes, statistics, the caller's radii); model: its
+// radii come from a model.
+Route call_route(kd_tree t, int K, int64_t Q, bool lanes_only, bool model);
 
 // One job of a batched call, as the device sees it.  Jobs of one (dim, K)
 // class are laid out back to back in a class slot space.
@@ -365,8 +376,10 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
 // Validation shared by the query entry points (nothing enqueued on error).
 kd_status check_query_args_public(kd_tree t, const float* queries, int64_t Q, int k, float maxRadius,
                                   const int32_t* out_idx, const char* fn);
-// Launch plan for (tree, k) from opts, else the tree's tuned options, else defaults.
-kd_status resolve_plan_public(kd_tree t, int k, float maxRadius, const kd_opts* o, QueryPlan& p);
+// Launch plan for (tree, k) from opts, else what the tree's tuned options give a
+// call of Q queries on that route, else defaults.
+kd_status resolve_plan_public(kd_tree t, int k, float maxRadius, const kd_opts* o, int64_t Q, Route route,
+                              QueryPlan& p);
 // Validated plain kNN: empty trees answered without traversal, else run_knn.
 kd_status knn_entry(kd_tree t, const float* queries, int64_t Q, int k, float maxRadius, int32_t* out_idx,
                     float* out_d2, uint32_t* visited, const kd_opts* opts, kd_stream stream, const char* fn,

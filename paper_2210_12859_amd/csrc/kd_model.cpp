@@ -319,7 +319,8 @@ kd_status kd_knn_learned(kd_tree t, kd_model m, const float* queries, int64_t Q,
     if (Q == 0 || t->N == 0)
         return knn_entry(t, queries, Q, k, maxRadius, out_idx, out_d2, visited, opts, stream, "kd_knn_learned");
     QueryPlan plan;
-    s = resolve_plan_public(t, k, maxRadius, opts, plan);
+    s = resolve_plan_public(t, k, maxRadius, opts, Q,
+                            call_route(t, k_template(k), Q, visited != nullptr || stats != nullptr, true), plan);
     if (s != KD_OK) return s;
     LearnedSpec ls{};
     ls.params = m->d_params;
@@ -344,7 +345,7 @@ kd_status kd_knn_with_radius(kd_tree t, const float* r0, const float* queries, i
         return s;
     }
     QueryPlan plan;
-    s = resolve_plan_public(t, k, maxRadius, opts, plan);
+    s = resolve_plan_public(t, k, maxRadius, opts, Q, Route::lanes, plan);
     if (s != KD_OK) return s;
     LearnedSpec ls{};
     ls.r0 = r0;

@@ -1603,6 +1603,14 @@ bool batch_by_wave(int dim, int K, int64_t n) { return n <= std::min(wave_querie
 
 bool batch_packet_job(kd_tree t, int K, int64_t Q) { return use_packets(t, K, Q); }
 
+Route call_route(kd_tree t, int K, int64_t Q, bool lanes_only, bool model) {
+    if (lanes_only || t->N == 0 || Q == 0) return Route::lanes;
+    if (!model && Q <= wave_queries(t->dim, K)) return Route::wave;
+    // without a first walk sparse queries cost more (2M points, 300,000 queries,
+    // k = 8: 0.34 lane by lane, 0.53 ms)
+    return use_packets(t, K, Q) && (!model || Q >= t->N / 2) ? Route::packets : Route::lanes;
+}
+
 kd_status run_batch_packets(const BatchJob* d_jobs, int njobs, int dim, int K, uint32_t n, uint32_t packets,
                             const uint32_t* perm, void* recs, uint32_t* counters, int device, hipStream_t st) {
     if (n == 0) return KD_OK;
@@ -1660,8 +1668,10 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
     // radii from a model suit packets as queries do, those of the caller may be
     // anything (three times too large: lane by lane 0.52, packets 0.72 ms) and
     // keep the lanes, as do counts of restarts
-    const bool plain = plan.plain && !visited && !stats && !(learned && !learned->params);
-    const bool by_wave = plain && !learned && Q <= wave_queries(t->dim, plan.K);
+    const Route route = plan.plain ? call_route(t, plan.K, Q, visited || stats || (learned && !learned->params),
+                                                learned != nullptr)
+                                   : Route::lanes;
+    const bool by_wave = route == Route::wave, packet = route == Route::packets;
     if (by_wave && Q <= WAVE_UNSORTED) {
         hipEvent_t ev = nullptr;
         if (!fixed) {
@@ -1679,9 +1689,6 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
         if (we != hipSuccess) return hip_error(we, "knn_wave launch");
         return timing_end(st, ev, "traverse");
     }
-    // without a first walk sparse queries cost more (2M points, 300,000 queries,
-    // k = 8: 0.34 lane by lane, 0.53 ms)
-    const bool packet = plain && !by_wave && use_packets(t, plan.K, Q) && (!learned || Q >= t->N / 2);
     const size_t cursor_bytes = size_t(MAX_GROUPS) * CURSOR_STRIDE * 4;  // 256 KB
     const size_t head = cursor_bytes + 4096;
     const size_t sq_bytes = (size_t(Q) * rec_bytes(t->dim) + 255) & ~size_t(255);

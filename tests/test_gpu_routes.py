@@ -56,3 +56,24 @@ def test_packet_rows(oracle_lib, dim, k):
         ri, rd, _ = oracle_lib.knn(P, order, Qs, k, r)
         assert np.array_equal(i.reshape(ri.shape), ri)
         assert np.array_equal(d.reshape(rd.shape).view(np.uint32), rd.view(np.uint32))
+
+
+def test_tuned_trees_keep_the_kernels(oracle_lib):
+    """Options tuned where calls go lane by lane (or set by the caller) leave
+    small calls to one wave per query; rows are the oracle's throughout."""
+    import paper_2210_12859_amd as kd
+    rng = np.random.default_rng(7)
+    P, Qs = _data(rng, 1_000_000, 3), _data(rng, 110_000, 3)  # above the line, too sparse for packets
+    order = oracle_lib.build_tree(P)
+    ri, rd, _ = oracle_lib.knn(P, order, Qs, 8)
+    set_tree, tuned_tree = (kd.kd_build(torch.from_numpy(P).to("cuda:0")) for _ in range(2))
+    lanes = dict(block=512, lds_levels=0, sort_bits=24, waves_per_cu=16, heavy_trips=0, prune=2)
+    kd.kd_tree_set_tuned(set_tree, 8, lanes)
+    best, _ = kd.kd_autotune(tuned_tree, torch.from_numpy(Qs).to("cuda:0"), 8)
+    assert kd.kd_tree_get_tuned(set_tree, 8) == lanes and kd.kd_tree_get_tuned(tuned_tree, 8) == best
+    for tree in (set_tree, tuned_tree):
+        for q, sorted_ in ((250, 0), (20_000, 0), (110_000, 1)):
+            print(f"[gpu] tuned Q={q}", flush=True)
+            i, d, sorts = _call(kd, tree, Qs[:q], 8)
+            assert sorts == sorted_
+            assert np.array_equal(i, ri[:q]) and np.array_equal(d.view(np.uint32), rd[:q].view(np.uint32))
