@@ -458,7 +458,9 @@ typedef struct kd_batch_s* kd_batch;
  *   opts  : nullable; block, waves_per_cu, sort_bits, heavy_trips and prune
  *           apply to every group (waves_per_cu 0: 32 for k = 1, else 24;
  *           sort_bits -1: 16 Morton bits below the group's job-index bits,
- *           rounded up to whole bytes). */
+ *           rounded up to whole bytes).  A group whose values all are its
+ *           defaults, spelled out or not, also takes the kernel that suits its
+ *           size, as kd_knn does. */
 kd_status kd_batch_create(const kd_job* jobs, int n_jobs, kd_model model, const kd_opts* opts, kd_stream stream,
                           kd_batch* out);
 /* Replays the captured graph on stream (asynchronous). */
@@ -472,10 +474,11 @@ kd_status kd_knn_batched(const kd_job* jobs, int n_jobs, kd_model model, const k
  * 256 / 512 x waves per CU 16 / 24 / 32 x sort key bits 16 / 24 / 32), reps
  * timed runs each, checks that every candidate writes the same outputs (a
  * 64-bit checksum of the group's result rows; a difference is KD_EHIP), keeps
- * the fastest per group and captures the graph again.  Overwrites the jobs'
+ * the fastest per group and captures the graph again; the plans stay as they
+ * were where the new graph as a whole is not faster.  Overwrites the jobs'
  * outputs (with the same results).  class_opts (HOST, nullable, n_classes
- * entries on input) receives the options kept per group, in kd_batch_info's
- * order; *n_classes (nullable) the number of groups.  Synchronises. */
+ * entries on input) receives the options kept per group (kd_batch_create makes
+ * the group's plan from them again), in kd_batch_info's order; *n_classes (nullable) the number of groups.  Synchronises. */
 kd_status kd_batch_autotune(kd_batch b, int reps, kd_stream stream, kd_opts* class_opts, int* n_classes);
 /* The groups of a batch (HOST arrays of cap entries, each nullable):
  * dimension, compiled list size, query count. */

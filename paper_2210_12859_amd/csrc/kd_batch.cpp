@@ -41,6 +41,7 @@ struct kd_batch_s {
         uint32_t packets = 0;
         bool other_kernels() const { return plan.plain && (by_wave || packets); }
         kd::QueryPlan plan;
+        int default_bits = 0, default_waves = 0;  // sort bits and waves of the class at default options
         float est_ms = 0.0f;             // expected pipeline time: measured by the autotuner, else estimated
     };
     std::vector<Class> classes;
@@ -146,6 +147,13 @@ float class_cost_estimate(int dim, int K, uint32_t n) {
     }
     const float df = dim == 2 ? 0.7f : (dim == 3 ? 1.0f : 1.7f);
     return float(n) * 0.67e-6f * kf * df;
+}
+
+// Whether a plan's values are the class's at default options, given as such or
+// spelled out: the class then takes the kernels its size chooses.
+bool at_defaults(const kd_batch_s::Class& c, const QueryPlan& p) {
+    return p.block == 256 && p.lds_levels == 0 && p.sort_bits == c.default_bits &&
+           p.waves_per_cu == c.default_waves && p.heavy_default && p.prune == 0;
 }
 
 // The whole pipeline of one class on stream st.
@@ -367,14 +375,15 @@ kd_status kd_batch_create(const kd_job* jobs, int n_jobs, kd_model model, const 
         c.jobs = kv.second;
         c.plan = base;
         c.plan.K = c.K;
-        if (!opts || opts->waves_per_cu == 0) c.plan.waves_per_cu = c.K == 1 ? 32 : 24;
-        if (!opts || opts->sort_bits < 0) {
-            // the job index takes the top bits of the sort key: keep 16 bits
-            // of Morton code below it
-            int jb = 0;
-            while ((1 << jb) < c.njobs) ++jb;
-            c.plan.sort_bits = std::min(32, ((jb + 16 + 7) / 8) * 8);
-        }
+        c.default_waves = c.K == 1 ? 32 : 24;
+        if (!opts || opts->waves_per_cu == 0) c.plan.waves_per_cu = c.default_waves;
+        // the job index takes the top bits of the sort key: keep 16 bits of
+        // Morton code below it
+        int jb = 0;
+        while ((1 << jb) < c.njobs) ++jb;
+        c.default_bits = std::min(32, ((jb + 16 + 7) / 8) * 8);
+        if (!opts || opts->sort_bits < 0) c.plan.sort_bits = c.default_bits;
+        c.plan.plain = at_defaults(c, c.plan);
         c.est_ms = class_cost_estimate(c.dim, c.K, c.n);
         if (mlp.find(kv.first) == mlp.end()) {
             // the classes share the GPU, so the line is for their sum
@@ -462,8 +471,32 @@ kd_status kd_batch_autotune(kd_batch b, int reps, kd_stream stream, kd_opts* cla
         *h = v;
         return KD_OK;
     };
-    kd_status s = KD_OK;
+    // ms per replay of the whole batch, on the caller's stream: which hardware
+    // queues the branches share depends on it (512 trees, the same graph: 110.0 ms
+    // on the default stream, 106.7 on one of its own)
+    hipStream_t user = reinterpret_cast<hipStream_t>(stream);
+    auto time_graph = [&](float* ms) -> kd_status {
+        KD_HIP(hipStreamSynchronize(st));
+        for (int r = 0; r < 3; ++r) KD_HIP(hipGraphLaunch(b->exec, user));  // a fresh graph's first replays are slower
+        const int n = std::max(reps, 3);
+        KD_HIP(hipEventRecord(e0, user));
+        for (int r = 0; r < n; ++r) KD_HIP(hipGraphLaunch(b->exec, user));
+        KD_HIP(hipEventRecord(e1, user));
+        KD_HIP(hipEventSynchronize(e1));
+        KD_HIP(hipEventElapsedTime(ms, e0, e1));
+        *ms /= float(n);
+        return KD_OK;
+    };
+    struct Before {
+        QueryPlan plan;
+        float est_ms;
+    };
+    std::vector<Before> before;
+    for (const auto& c : b->classes) before.push_back({c.plan, c.est_ms});
+    float ms_before = 0.0f, ms_tuned = 0.0f;
+    kd_status s = time_graph(&ms_before);
     for (auto& c : b->classes) {
+        if (s != KD_OK) break;
         // candidates: workgroup size x waves per CU x Morton sort bits
         const QueryPlan keep = c.plan;
         QueryPlan best = keep;
@@ -515,13 +548,28 @@ kd_status kd_batch_autotune(kd_batch b, int reps, kd_stream stream, kd_opts* cla
         if (s != KD_OK) break;
     }
     if (s == KD_OK) s = capture_batch(b, reinterpret_cast<hipStream_t>(stream));
+    if (s == KD_OK) s = time_graph(&ms_tuned);
+    if (s == KD_OK && ms_tuned >= ms_before) {
+        // the classes were timed one by one, but share the GPU in the graph: where
+        // that made the whole slower, the plans stay (512 trees: 109.7 ms with
+        // the options chosen one by one, 107.6 with the defaults)
+        for (size_t i = 0; i < before.size(); ++i) {
+            b->classes[i].plan = before[i].plan;
+            b->classes[i].est_ms = before[i].est_ms;
+        }
+        s = capture_batch(b, reinterpret_cast<hipStream_t>(stream));
+    }
     if (s == KD_OK && n_classes) {
         const int cap = *n_classes;
         *n_classes = int(b->classes.size());
         for (int i = 0; class_opts && i < cap && i < int(b->classes.size()); ++i) {
-            const QueryPlan& p = b->classes[i].plan;
-            class_opts[i] = kd_opts{p.plain ? 256 : p.block, p.lds_levels, p.sort_bits, p.waves_per_cu,
-                                    p.heavy_default ? 0 : (p.heavy_trips > 0 ? p.heavy_trips : -1), p.prune};
+            // given back to kd_batch_create they make the same plan: a lane plan
+            // with the defaults' values spells out its trip budget too
+            const kd_batch_s::Class& c = b->classes[i];
+            const QueryPlan& p = c.plan;
+            int trips = p.heavy_default ? 0 : (p.heavy_trips > 0 ? p.heavy_trips : -1);
+            if (!p.plain && at_defaults(c, p)) trips = KD_DEFAULT_HEAVY_TRIPS_BOXES;
+            class_opts[i] = kd_opts{p.block, p.lds_levels, p.sort_bits, p.waves_per_cu, trips, p.prune};
         }
     }
     cleanup();

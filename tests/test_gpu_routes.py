@@ -77,3 +77,43 @@ def test_tuned_trees_keep_the_kernels(oracle_lib):
             i, d, sorts = _call(kd, tree, Qs[:q], 8)
             assert sorts == sorted_
             assert np.array_equal(i, ri[:q]) and np.array_equal(d.view(np.uint32), rd[:q].view(np.uint32))
+
+
+def test_batch_options_make_the_kept_plan_again():
+    """A group that kept one wave per query: a batch made from the options that
+    the tuner returned takes them too (lane by lane a replay takes 10 times as
+    long), and tuning leaves no batch slower."""
+    import paper_2210_12859_amd as kd
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(3)
+    jobs = []
+    for i in range(8):
+        tree = kd.kd_build(torch.rand((10000, 3), generator=g, device="cuda:0"))
+        q = torch.rand((250, 3), generator=g, device="cuda:0")
+        jobs.append(dict(tree=tree, queries=q, k=8, out_idx=torch.empty((250, 8), dtype=torch.int32, device="cuda:0"),
+                         out_d2=torch.empty((250, 8), dtype=torch.float32, device="cuda:0")))
+
+    def ms(b):
+        best = np.inf
+        for _ in range(10):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            b.run()
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        return best
+
+    print("[gpu] batch options", flush=True)
+    b = kd.Batch(jobs)
+    t_default = ms(b)
+    rows = [j["out_idx"].clone() for j in jobs]
+    chosen = b.autotune(reps=1)
+    assert len(chosen) == 1
+    again, lanes = kd.Batch(jobs, opts=chosen[0]), kd.Batch(jobs, opts=dict(block=512))
+    t_tuned, t_again, t_lanes = ms(b), ms(again), ms(lanes)
+    print(f"[gpu] default {t_default:.4f} tuned {t_tuned:.4f} again {t_again:.4f} lanes {t_lanes:.4f} ms", flush=True)
+    assert t_tuned < 0.5 * t_lanes and t_again < 0.5 * t_lanes
+    again.run()
+    torch.cuda.synchronize()
+    assert all(torch.equal(j["out_idx"], r) for j, r in zip(jobs, rows))
