@@ -411,30 +411,58 @@ kd_status kd_build_ex(const float* points, int64_t N, int dim, int split, kd_str
     // (500 + 340 us at 300K points, measured call by call).
     struct Block {
         void* p = nullptr;
-        ~Block() { (void)hipFree(p); }
+        ~Block() { free(); }
         hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes); }
+        void free() { (void)hipFree(keep()); }
         void* keep() { return std::exchange(p, nullptr); }
-    } nodes, boxes, dims, ws;
-    KD_HIP(nodes.alloc(node_buffer_bytes(dim, N)));
-    KD_HIP(boxes.alloc(box_buffer_bytes(dim, N)));
-    if (widest) KD_HIP(dims.alloc(size_t(N) + 2));
-    // workspace: order + box + mark | split dimensions by position | the builder's
+    } nodes, boxes, dims, kept, ws;
+    auto alloc_tree = [&]() -> hipError_t {
+        hipError_t e = nodes.alloc(node_buffer_bytes(dim, N));
+        if (e == hipSuccess) e = boxes.alloc(box_buffer_bytes(dim, N));
+        if (e == hipSuccess && widest) e = dims.alloc(size_t(N) + 2);
+        return e;
+    };
+    // order + box + mark | split dimensions by position (kept) | the builder's workspace
     const size_t back_b = (back * 4 + 255) & ~size_t(255);
-    const size_t dims_b = widest ? (size_t(N) + 255) & ~size_t(255) : 0;
-    KD_HIP(ws.alloc(back_b + dims_b + build_scratch_bytes(N, dim, widest)));
-    int32_t* d_order = static_cast<int32_t*>(ws.p);
+    const size_t kept_b = back_b + (widest ? (size_t(N) + 255) & ~size_t(255) : 0);
+    hipError_t e = alloc_tree();
+    if (e == hipSuccess) e = ws.alloc(kept_b + build_scratch_bytes(N, dim, widest, false));
+    // Where they do not fit side by side, with the least workspace and the tree
+    // after it: at most the larger of (2 dim + 4) x 4 bytes a point and the tree's
+    // 32 (2-D) to 64 (4-D), beside the order's 4.
+    const bool tight = e == hipErrorOutOfMemory;
+    if (tight) {
+        (void)hipGetLastError();
+        for (Block* b : {&nodes, &boxes, &dims}) b->free();
+        e = kept.alloc(kept_b);
+        if (e == hipSuccess) e = ws.alloc(build_scratch_bytes(N, dim, widest, true));
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return hip_error(e, "kd_build: device memory");
+    }
+    int32_t* d_order = static_cast<int32_t*>(tight ? kept.p : ws.p);
     float* d_root = reinterpret_cast<float*>(d_order + N);
     uint32_t* d_bad = reinterpret_cast<uint32_t*>(d_root + 8);
-    char* rest = static_cast<char*>(ws.p) + back_b;
-    uint8_t* d_pos_dims = widest ? reinterpret_cast<uint8_t*>(rest) : nullptr;
+    uint8_t* d_pos_dims = widest ? reinterpret_cast<uint8_t*>(d_order) + back_b : nullptr;
+    void* scratch_ws = tight ? ws.p : static_cast<char*>(ws.p) + kept_b;
     KD_HIP(hipMemsetAsync(d_bad, 0, 4, st));
-    kd_status s = build_level_order_device(points, N, dim, d_order, d_bad, rest + dims_b, st, d_pos_dims);
+    kd_status s = build_level_order_device(points, N, dim, d_order, d_bad, scratch_ws, tight, st, d_pos_dims);
+    if (s == KD_OK && tight) {
+        e = hipStreamSynchronize(st);
+        ws.free();
+        if (e == hipSuccess) e = alloc_tree();
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            s = hip_error(e, "kd_build: device memory");
+        }
+    }
     if (s == KD_OK)
         s = pack_tree_device(points, d_order, N, dim, nodes.p, static_cast<float*>(boxes.p), d_root, st, d_pos_dims,
                              static_cast<uint8_t*>(dims.p));
     if (s == KD_OK) s = read_back(t.get(), d_order, back, d_pos_dims, st);
     // also after an error: what was launched uses the buffers freed here
-    const hipError_t e = hipStreamSynchronize(st);
+    e = hipStreamSynchronize(st);
     if (s != KD_OK) return s;
     if (e != hipSuccess) return hip_error(e, "kd_build: read back");
     if (t->order[back - 1] != 0) return set_error(KD_EINVAL, "kd_build: points contain NaN or inf");

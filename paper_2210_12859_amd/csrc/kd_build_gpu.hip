@@ -34,7 +34,7 @@
 // finishing one 45).  With a sort of the level's list by segment on every level
 // instead it was 190 launches; kd_build, allocations and read-back included,
 // sorts -> now, us: 1000 3-D points 540 -> 150, 100K 1220 -> 390, 300K 2180 ->
-// 540, 1M 3040 -> 1450, 10M 24.3 -> 15.0 ms.
+// 540, 1M 3040 -> 1450, 10M 24.3 -> 13.9 ms.
 //
 // Stored split dimensions (the widest rule): every segment of the level
 // picks its own dimension, so all D lists are sorted by segment each level.
@@ -94,11 +94,12 @@ struct Shape {
     }
 };
 
-__global__ void dim_keys(const float* __restrict__ pts, uint32_t N, int D, size_t stride, uint32_t* __restrict__ k,
-                         uint32_t* __restrict__ v, uint32_t* __restrict__ bad) {
+// of dimensions d0, d0 + 1, ...
+__global__ void dim_keys(const float* __restrict__ pts, uint32_t N, int D, int d0, size_t stride,
+                         uint32_t* __restrict__ k, uint32_t* __restrict__ v, uint32_t* __restrict__ bad) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
-    const float f = pts[size_t(i) * D + blockIdx.y];
+    const float f = pts[size_t(i) * D + d0 + blockIdx.y];
     if (!__builtin_isfinite(f)) *bad = 1u;
     k[blockIdx.y * stride + i] = coord_key(f);
     v[blockIdx.y * stride + i] = i;
@@ -259,17 +260,20 @@ __global__ __launch_bounds__(256) void level_locate(const uint32_t* __restrict__
     }
 }
 
-// Sort keys that group the lists by segment (placed points last).
-__global__ void group_keys(const uint32_t* __restrict__ L, uint32_t R, size_t stride, Pending pend,
-                           uint32_t placed_key, uint32_t* __restrict__ seg_out, uint32_t* __restrict__ k) {
+// Sort keys that group the lists by segment (placed points last).  applied:
+// seg_out holds the segments after the last split already (it may be the
+// split's own array).
+__global__ void group_keys(const uint32_t* __restrict__ L, uint32_t R, size_t stride, Pending pend, bool applied,
+                           uint32_t placed_key, uint32_t* seg_out, uint32_t* __restrict__ k) {
     const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= R) return;
     const uint32_t p[1] = {L[blockIdx.y * stride + j]};
     const bool valid[1] = {true};
     uint32_t s[1];
-    pend.children(p, valid, blockIdx.y == 0, s);
+    if (applied) s[0] = seg_out[p[0]];
+    else pend.children(p, valid, blockIdx.y == 0, s);
     k[blockIdx.y * stride + j] = s[0] == PLACED ? placed_key : s[0];
-    if (blockIdx.y == 0) seg_out[p[0]] = s[0];
+    if (blockIdx.y == 0 && !applied) seg_out[p[0]] = s[0];
 }
 
 // The levels from `top` on, one segment of that level per workgroup: its
@@ -630,35 +634,51 @@ int tree_levels(int64_t N) {  // floor(log2 N) + 1
 
 constexpr int GROUP_LEVELS = 10;  // top levels before the lists are grouped a first time
 
-// Workspace of a build by level: 4 (or 5) x D lists, three arrays by point or
-// list entry, two levels of splits, tile counts, sort counts.
+// The lists of all dimensions are sorted together, or one after another: where
+// each fills the GPU, and where memory is short.  One after another needs keys
+// and values to sort into for one list only.  Together / one by one, ms: by level
+// 2.1M 2-D to 4-D points 2.77 / 2.79, 3.07 / 3.20, 3.45 / 3.62; 4.2M 5.30 / 5.19,
+// 6.00 / 5.88, 6.82 / 6.57; 10M 12.9 / 12.3, 15.1 / 14.0, 17.3 / 15.6; 3-D by the
+// widest rule 2.1M 7.95 / 9.56, 4.2M 17.6 / 18.9, 10M 50.8 / 48.7.
+bool one_by_one(int64_t N, bool widest, bool tight) { return tight || N >= int64_t(1) << (widest ? 23 : 22); }
+
+// Workspace of a build by level: lists, ranks and a segment array; all lists
+// together: keys and values to sort them into (keys in the place of the ranks
+// unless the lists are grouped twice), two more segment arrays and tile counts;
+// one by one: three arrays for the sort, two of which the levels use too.  Then
+// two levels of splits and sort counts.
 struct LevelLayout {
     size_t stride, lists, one, splits, hist, sort, total;
     int top;
-    LevelLayout(int64_t N, int D) {
+    bool single, spare;
+    LevelLayout(int64_t N, int D, bool tight) {
         const int H = tree_levels(N);
         top = H > SUB_LEVELS ? H - SUB_LEVELS : 0;
+        single = one_by_one(N, false, tight);
+        spare = top > GROUP_LEVELS;
         stride = pad(size_t(N) * 4) / 4;
         lists = stride * 4 * size_t(D);
         one = stride * 4;
         splits = pad((size_t(1) << top) * 4);
-        hist = top > 1 ? pad((size_t(N) / TILE + 1) * 4 * MAX_COUNTERS) : 0;
-        sort = pad(sort_pairs_scratch_bytes(uint32_t(N)) * size_t(D));
-        total = lists * (top > GROUP_LEVELS ? 5 : 4) + one * 3 + splits * 2 + hist + sort;
+        hist = top > 1 ? pad((size_t(N) / TILE + 1) * 4 * (spare ? MAX_COUNTERS : 1u << (top - 1))) : 0;
+        sort = pad(sort_pairs_scratch_bytes(uint32_t(N)) * size_t(single ? 1 : D));
+        total = (single ? lists * 2 + one * 4 : lists * (spare ? 5 : 4) + one * 3 + hist) + splits * 2 + sort;
     }
 };
 
 // Workspace of a build by the widest rule: lists sorted by coordinate and by
-// segment, two pair buffers, two segment arrays, segment dimensions.
+// segment, what the sorts need, two segment arrays, segment dimensions.
 struct WidestLayout {
     size_t stride, lists, one, dims, sort, total;
-    WidestLayout(int64_t N, int D) {
+    bool single;
+    WidestLayout(int64_t N, int D, bool tight) {
+        single = one_by_one(N, true, tight);
         stride = pad(size_t(N) * 4) / 4;
         lists = stride * 4 * size_t(D);
         one = stride * 4;
         dims = pad(size_t(N));
-        sort = pad(sort_pairs_scratch_bytes(uint32_t(N)) * size_t(D));
-        total = lists * 5 + one * 2 + dims + sort;
+        sort = pad(sort_pairs_scratch_bytes(uint32_t(N)) * size_t(single ? 1 : D));
+        total = lists * 2 + (single ? one : lists) * 3 + one * 2 + dims + sort;
     }
 };
 
@@ -672,53 +692,73 @@ struct Carve {
     }
 };
 
-// L_d for every dimension, in va (vb, ka, kb are workspace).
-kd_status sorted_lists(const float* d_pts, uint32_t n, int D, size_t stride, uint32_t* ka, uint32_t* va, uint32_t* kb,
-                       uint32_t* vb, void* sort, uint32_t* d_bad, hipStream_t st) {
-    hipLaunchKernelGGL(dim_keys, dim3(grid_for(n).x, D), dim3(256), 0, st, d_pts, n, D, stride, ka, va, d_bad);
-    KD_HIP(hipGetLastError());
-    bool second = false;  // four passes: back in the first pair
-    return sort_pairs(ka, va, kb, vb, n, 32, sort, st, &second, D, stride);
+// L_d for every dimension, in L (ka, kb, vb are workspace).
+kd_status sorted_lists(const float* d_pts, uint32_t n, int D, size_t stride, bool single, uint32_t* ka, uint32_t* L,
+                       uint32_t* kb, uint32_t* vb, void* sort, uint32_t* d_bad, hipStream_t st) {
+    const int step = single ? 1 : D;
+    for (int d = 0; d < D; d += step) {
+        uint32_t* va = L + size_t(d) * stride;
+        hipLaunchKernelGGL(dim_keys, dim3(grid_for(n).x, step), dim3(256), 0, st, d_pts, n, D, d, stride, ka, va,
+                           d_bad);
+        KD_HIP(hipGetLastError());
+        bool second = false;  // four passes: back in the first pair
+        const kd_status s = sort_pairs(ka, va, kb, vb, n, 32, sort, st, &second, step, stride);
+        if (s != KD_OK) return s;
+    }
+    return KD_OK;
 }
 
 kd_status build_widest_device(const float* d_pts, int64_t N, int D, int32_t* d_order, uint32_t* d_bad, void* ws,
-                              uint8_t* d_pos_dims, hipStream_t st) {
+                              uint8_t* d_pos_dims, bool tight, hipStream_t st) {
     const uint32_t n = uint32_t(N);
-    const WidestLayout lay(N, D);
+    const WidestLayout lay(N, D, tight);
+    const size_t stride = lay.stride;
     Carve c{static_cast<char*>(ws)};
     uint32_t* L = c.take(lay.lists);   // by coordinate
-    uint32_t* k0 = c.take(lay.lists);
-    uint32_t* v0 = c.take(lay.lists);
-    uint32_t* k1 = c.take(lay.lists);
-    uint32_t* v1 = c.take(lay.lists);
+    uint32_t* v0 = c.take(lay.lists);  // by segment
+    uint32_t* k0 = c.take(lay.single ? lay.one : lay.lists);
+    uint32_t* k1 = c.take(lay.single ? lay.one : lay.lists);
+    uint32_t* v1 = c.take(lay.single ? lay.one : lay.lists);
     uint32_t* seg = c.take(lay.one);
     uint32_t* seg_next = c.take(lay.one);
     uint8_t* segdim = c.take<uint8_t>(lay.dims);
     void* sort = c.p;
     const dim3 g = grid_for(n), b(256);
-    kd_status s = sorted_lists(d_pts, n, D, lay.stride, k0, L, k1, v1, sort, d_bad, st);
+    kd_status s = sorted_lists(d_pts, n, D, stride, lay.single, k0, L, k1, v1, sort, d_bad, st);
     if (s != KD_OK) return s;
     hipLaunchKernelGGL(fill_u32, g, b, 0, st, seg, n, 0u);
     KD_HIP(hipGetLastError());
     const int H = tree_levels(N);
     const int64_t last = N - ((int64_t(1) << (H - 1)) - 1);
+    const int step = lay.single ? 1 : D;
     for (int l = 0; l < H; ++l) {
         const int64_t first = (int64_t(1) << l) - 1;
         const uint32_t R = uint32_t(N - first);
         const int64_t W = int64_t(1) << (H - 1 - l);
-        hipLaunchKernelGGL(level_keys, dim3(g.x, D), b, 0, st, L, seg, n, lay.stride, uint32_t(1) << l, k0, v0);
-        KD_HIP(hipGetLastError());
-        bool second = false;
-        s = sort_pairs(k0, v0, k1, v1, n, l + 1, sort, st, &second, D, lay.stride);
-        if (s != KD_OK) return s;
-        const uint32_t* S = second ? v1 : v0;
+        const uint32_t* S = v0;
+        for (int d = 0; d < D; d += step) {
+            uint32_t* vd = v0 + size_t(d) * stride;
+            // one by one the sorted list has to end in v0: with an odd number of
+            // passes it starts in v1
+            const bool odd = lay.single && ((l + 1 + 7) / 8) % 2 == 1;
+            uint32_t *ka = odd ? k1 : k0, *va = odd ? v1 : vd, *kb = odd ? k0 : k1, *vb = odd ? vd : v1;
+            hipLaunchKernelGGL(level_keys, dim3(g.x, step), b, 0, st, L + size_t(d) * stride, seg, n, stride,
+                               uint32_t(1) << l, ka, va);
+            KD_HIP(hipGetLastError());
+            bool second = false;
+            s = sort_pairs(ka, va, kb, vb, n, l + 1, sort, st, &second, step, stride);
+            if (s != KD_OK) return s;
+            // (one point is not sorted at all, and lies where it was written)
+            if (!lay.single) S = second ? v1 : v0;
+            else if (odd && !second) KD_HIP(hipMemcpyAsync(vd, va, size_t(n) * 4, hipMemcpyDeviceToDevice, st));
+        }
         const int64_t nodes = std::min<int64_t>(int64_t(1) << l, N - first);
-        hipLaunchKernelGGL(segment_dims, grid_for(uint64_t(nodes)), b, 0, st, d_pts, D, S, lay.stride, uint32_t(nodes),
-                           W, last, first, segdim, d_pos_dims);
+        hipLaunchKernelGGL(segment_dims, grid_for(uint64_t(nodes)), b, 0, st, d_pts, D, S, stride, uint32_t(nodes), W,
+                           last, first, segdim, d_pos_dims);
         KD_HIP(hipGetLastError());
         KD_HIP(hipMemcpyAsync(seg_next, seg, size_t(n) * 4, hipMemcpyDeviceToDevice, st));
-        hipLaunchKernelGGL(level_assign_widest, dim3(grid_for(R).x, D), b, 0, st, S, lay.stride, segdim, seg, R, W,
-                           last, first, d_order, seg_next);
+        hipLaunchKernelGGL(level_assign_widest, dim3(grid_for(R).x, D), b, 0, st, S, stride, segdim, seg, R, W, last,
+                           first, d_order, seg_next);
         KD_HIP(hipGetLastError());
         std::swap(seg, seg_next);
     }
@@ -726,24 +766,37 @@ kd_status build_widest_device(const float* d_pts, int64_t N, int D, int32_t* d_o
 }
 
 template <int D>
-kd_status build_by_level(const float* d_pts, int64_t N, int32_t* d_order, uint32_t* d_bad, void* ws, hipStream_t st) {
+kd_status build_by_level(const float* d_pts, int64_t N, int32_t* d_order, uint32_t* d_bad, void* ws, bool tight,
+                         hipStream_t st) {
     const uint32_t n = uint32_t(N);
-    const LevelLayout lay(N, D);
+    const LevelLayout lay(N, D, tight);
     const size_t stride = lay.stride;
+    const bool single = lay.single;
     Carve c{static_cast<char*>(ws)};
     uint32_t* L = c.take(lay.lists);
-    uint32_t* L2 = c.take(lay.lists);
-    uint32_t* keys = c.take(lay.lists);
     uint32_t* rank = c.take(lay.lists);
-    uint32_t* spare = lay.top > GROUP_LEVELS ? c.take(lay.lists) : nullptr;
     uint32_t* seg = c.take(lay.one);
-    uint32_t* seg2 = c.take(lay.one);
-    uint32_t* segL = c.take(lay.one);
+    // the sorts' keys, and the keys and values they sort into; segments by list
+    // entry, a second array of segments by point, tile counts
+    uint32_t *k0, *k1, *v1, *segL, *seg2, *hist;
+    if (single) {
+        k0 = segL = c.take(lay.one);
+        k1 = hist = c.take(lay.one);  // (N / 1024 + 1) 512 counts fit: N > 2047 where there are any
+        v1 = c.take(lay.one);
+        seg2 = seg;                   // each list's keys are made before the next list's
+    } else {
+        k0 = c.take(lay.lists);
+        // before the ranks are made, and when they are not needed any more
+        k1 = lay.spare ? c.take(lay.lists) : rank;
+        v1 = c.take(lay.lists);
+        segL = c.take(lay.one);
+        seg2 = c.take(lay.one);
+        hist = c.take(lay.hist);
+    }
     uint32_t* split = c.take(lay.splits);
     uint32_t* split2 = c.take(lay.splits);
-    uint32_t* hist = c.take(lay.hist);
     void* sort = c.p;
-    kd_status s = sorted_lists(d_pts, n, D, stride, keys, L, rank, L2, sort, d_bad, st);
+    kd_status s = sorted_lists(d_pts, n, D, stride, single, k0, L, k1, v1, sort, d_bad, st);
     if (s != KD_OK) return s;
     const int H = tree_levels(N), top = lay.top;
     const int64_t last = N - ((int64_t(1) << (H - 1)) - 1);  // nodes on the last level
@@ -756,16 +809,20 @@ kd_status build_by_level(const float* d_pts, int64_t N, int32_t* d_order, uint32
         return Pending{rank + size_t((l - 1) % D) * stride, split, seg_now, d_order + ((int64_t(1) << (l - 1)) - 1)};
     };
     auto group_lists = [&](int l) -> kd_status {
-        hipLaunchKernelGGL(group_keys, dim3(grid_for(R).x, D), dim3(256), 0, st, L, R, stride, pending(l),
-                           uint32_t(1) << l, seg2, keys);
-        KD_HIP(hipGetLastError());
+        const int step = single ? 1 : D;
+        for (int d = 0; d < D; d += step) {
+            uint32_t* Ld = L + size_t(d) * stride;
+            hipLaunchKernelGGL(group_keys, dim3(grid_for(R).x, step), dim3(256), 0, st, Ld, R, stride, pending(l),
+                               d > 0, uint32_t(1) << l, seg2, k0);
+            KD_HIP(hipGetLastError());
+            bool second = false;
+            const kd_status gs = sort_pairs(k0, Ld, k1, v1, R, l + 1, sort, st, &second, step, stride);
+            if (gs != KD_OK) return gs;
+            if (second && single) KD_HIP(hipMemcpyAsync(Ld, v1, size_t(R) * 4, hipMemcpyDeviceToDevice, st));
+            else if (second) std::swap(L, v1);
+        }
         seg_now = seg2;
         std::swap(seg, seg2);
-        bool second = false;
-        // after the last split the ranks are not needed any more
-        kd_status gs = sort_pairs(keys, L, l == top ? rank : spare, L2, R, l + 1, sort, st, &second, D, stride);
-        if (gs != KD_OK) return gs;
-        if (second) std::swap(L, L2);
         base = l;
         R = uint32_t(N - ((int64_t(1) << l) - 1));
         return KD_OK;
@@ -801,7 +858,7 @@ kd_status build_by_level(const float* d_pts, int64_t N, int32_t* d_order, uint32
         s = group_lists(top);
         if (s != KD_OK) return s;
     }
-    hipLaunchKernelGGL((build_subtree<D>), dim3(1u << top), dim3(64 * SUB_WAVES), 0, st, L, stride, seg2, top, H, last,
+    hipLaunchKernelGGL((build_subtree<D>), dim3(1u << top), dim3(64 * SUB_WAVES), 0, st, L, stride, segL, top, H, last,
                        d_order);
     KD_HIP(hipGetLastError());
     return KD_OK;
@@ -822,18 +879,18 @@ kd_status pack_tree(const float* d_pts, const int32_t* d_order, int64_t N, void*
 
 }  // namespace
 
-size_t build_scratch_bytes(int64_t N, int dim, bool widest) {
-    return widest ? WidestLayout(N, dim).total : LevelLayout(N, dim).total;
+size_t build_scratch_bytes(int64_t N, int dim, bool widest, bool tight) {
+    return widest ? WidestLayout(N, dim, tight).total : LevelLayout(N, dim, tight).total;
 }
 
 kd_status build_level_order_device(const float* d_pts, int64_t N, int D, int32_t* d_order, uint32_t* d_bad, void* ws,
-                                   hipStream_t st, uint8_t* d_pos_dims) {
+                                   bool tight, hipStream_t st, uint8_t* d_pos_dims) {
     if (N <= 0) return KD_OK;
-    if (d_pos_dims) return build_widest_device(d_pts, N, D, d_order, d_bad, ws, d_pos_dims, st);
+    if (d_pos_dims) return build_widest_device(d_pts, N, D, d_order, d_bad, ws, d_pos_dims, tight, st);
     switch (D) {
-        case 2: return build_by_level<2>(d_pts, N, d_order, d_bad, ws, st);
-        case 3: return build_by_level<3>(d_pts, N, d_order, d_bad, ws, st);
-        default: return build_by_level<4>(d_pts, N, d_order, d_bad, ws, st);
+        case 2: return build_by_level<2>(d_pts, N, d_order, d_bad, ws, tight, st);
+        case 3: return build_by_level<3>(d_pts, N, d_order, d_bad, ws, tight, st);
+        default: return build_by_level<4>(d_pts, N, d_order, d_bad, ws, tight, st);
     }
 }
 

@@ -255,10 +255,10 @@ kd_status sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, uin
 // a NaN or infinite coordinate sets *d_bad.  d_pos_dims non-NULL: the
 // widest-extent rule, each position's split dimension written there (uint8
 // [N]); NULL: the dimension by level.  ws holds build_scratch_bytes and is in
-// use until the stream has passed.
-size_t build_scratch_bytes(int64_t N, int dim, bool widest);
+// use until the stream has passed.  tight: with the least workspace.
+size_t build_scratch_bytes(int64_t N, int dim, bool widest, bool tight);
 kd_status build_level_order_device(const float* d_pts, int64_t N, int dim, int32_t* d_order, uint32_t* d_bad, void* ws,
-                                   hipStream_t st, uint8_t* d_pos_dims = nullptr);
+                                   bool tight, hipStream_t st, uint8_t* d_pos_dims = nullptr);
 // Node records and subtree boxes from device points and order (kd_build_gpu.hip);
 // with stored dimensions (d_pos_dims by position) the records' ancestor splits
 // follow them and d_dims (uint8 [N + 2], by node id) receives the packed
