@@ -50,10 +50,15 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // Pairs of chunks held in LDS until their candidates are inserted and the bounds
-// refreshed.  More fill the insertions better, fewer refresh sooner: 1M uniform /
-// mixture points, 4 -> 2, ms: k = 1 0.300 -> 0.301 / 0.453 -> 0.435, k = 8 0.465
-// -> 0.474 / 0.719 -> 0.687, k = 16 and 32 0.721 -> 0.707 / 2.146 -> 2.115.
-constexpr int pairs_held(int K) { return K == 8 ? 4 : 2; }
+// refreshed.  More fill the insertions better, which uniform points gain by; fewer
+// refresh sooner, which clusters gain by, and more: 2 for every list.  1M points
+// and queries, 4 -> 2, ms, uniform / mixture / clusters of many widths: 3-D, k = 1
+// 0.332 -> 0.332 / 0.410 -> 0.381 / 0.740 -> 0.677, k = 4 0.395 -> 0.397 / 0.547
+// -> 0.532 / 0.946 -> 0.880, k = 8 0.466 -> 0.474 / 0.668 -> 0.660 / 1.237 ->
+// 1.197, k = 32 1.473 -> 1.474 / 2.134 -> 2.106 / 3.436 -> 3.275; 4-D, k = 8 0.939
+// -> 0.955 / 1.160 -> 1.171 / 2.639 -> 2.570; 3-D, k = 8 from a model's radii 0.847
+// -> 0.813 / 1.772 -> 1.657; 300,000 queries of the uniform points 0.289 -> 0.301.
+constexpr int NPEND = 2;
 // Entry of the chunks held that a queue byte names.  Lanes without a candidate
 // read bytes that nothing wrote, so every byte has to name one of the entries.
 __host__ __device__ constexpr uint32_t held_entry(uint32_t byte, uint32_t entries) { return byte & (entries - 1u); }
@@ -62,9 +67,7 @@ constexpr bool held_entries_hold(uint32_t entries) {
         if (held_entry(b, entries) >= entries || (b < entries && held_entry(b, entries) != b)) return false;
     return entries <= 256u;  // a queue entry is a byte
 }
-static_assert(held_entries_hold(pairs_held(1) * 64) && held_entries_hold(pairs_held(8) * 64) &&
-                  held_entries_hold(pairs_held(32) * 64),
-              "queue bytes");
+static_assert(held_entries_hold(NPEND * 64), "queue bytes");
 constexpr int QCAP = 16;        // candidates a query can hold until then
 constexpr uint32_t MAX_HOME = 8;          // chunk pairs of the first walk
 constexpr int SHORT_LISTS = 8;            // lists left short by initial radii that repeat a packet
@@ -266,7 +269,6 @@ __device__ __forceinline__ f32x16 products(const u32x4& a, const u32x4& b) {
 enum Source { CALL, RADII, JOBS };
 template <int D, int K, Source SRC>
 __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 : 5) : 1) void knn_packet(PacketArgs a) {
-    constexpr int NPEND = pairs_held(K);
     __shared__ float4 pt[NPEND * 64];                    // points of the chunks held
     __shared__ int32_t pid[D == 4 ? NPEND * 64 : 1];     // their caller indices where w is a coordinate
     __shared__ uint8_t queue[(QCAP + 1) * 64];           // candidate i of lane l at 64 i + l
