@@ -9,7 +9,8 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 # the longest call of one wave per query, by dimension and list size
-LINE = {(3, 8): 98304, (3, 16): 131072, (3, 32): 262144, (4, 8): 131072, (4, 16): 163840, (4, 32): 262144}
+LINE = {(2, 8): 65536, (2, 16): 98304, (2, 32): 131072, (3, 8): 98304, (3, 16): 131072, (3, 32): 262144,
+        (4, 8): 131072, (4, 16): 163840, (4, 32): 262144, (2, 64): 327680, (3, 64): 327680, (4, 64): 327680}
 
 
 def _data(rng, n, dim):
@@ -56,6 +57,22 @@ def test_packet_rows(oracle_lib, dim, k):
         ri, rd, _ = oracle_lib.knn(P, order, Qs, k, r)
         assert np.array_equal(i.reshape(ri.shape), ri)
         assert np.array_equal(d.reshape(rd.shape).view(np.uint32), rd.view(np.uint32))
+
+
+@pytest.mark.parametrize("dim,k", sorted(LINE))
+def test_lines(oracle_lib, dim, k):
+    """The longest call without a sort, and one more query."""
+    import paper_2210_12859_amd as kd
+    rng = np.random.default_rng(dim * 64 + k)
+    q = LINE[(dim, k)]
+    P, Qs = _data(rng, 50000, dim), _data(rng, q + 1, dim)
+    print(f"[gpu] line D={dim} k={k} Q={q}", flush=True)
+    tree = kd.kd_build(torch.from_numpy(P).to("cuda:0"))
+    ri, rd, _ = oracle_lib.knn(P, oracle_lib.build_tree(P), Qs, k)
+    for n, sorted_ in ((q, 0), (q + 1, 1)):
+        i, d, sorts = _call(kd, tree, Qs[:n], k)
+        assert sorts == sorted_
+        assert np.array_equal(i, ri[:n]) and np.array_equal(d.view(np.uint32), rd[:n].view(np.uint32))
 
 
 def test_tuned_trees_keep_the_kernels(oracle_lib):
