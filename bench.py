@@ -55,6 +55,10 @@ def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
+# the sources of the traversal kernel whose counters are committed
+TRAVERSE_SOURCES = [f"paper_2210_12859_amd/csrc/{f}" for f in ("kd_traverse.hip", "kd_internal.h", "kd_list.h")]
+
+
 def src_hash(paths):
     h = hashlib.sha256()
     for p in paths:
@@ -727,7 +731,7 @@ def main():
 
     alg_bytes = visited_total * D * 4  # node data touched per launch
     achieved = alg_bytes / (kern_avg_ms / 1e3) / 1e9
-    cur_hash = src_hash(["paper_2210_12859_amd/csrc/kd_traverse.hip", "paper_2210_12859_amd/csrc/kd_internal.h"])
+    cur_hash = src_hash(TRAVERSE_SOURCES)
     traffic = load_traffic(f"traverse_{args.workload}_k{k}", cur_hash, 1)
     counters = load_counters(f"traverse_{args.workload}_k{k}", cur_hash)
     # the secondary algorithmic total: node data plus each query read and its

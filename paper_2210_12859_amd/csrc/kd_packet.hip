@@ -254,9 +254,9 @@ __device__ __forceinline__ f32x16 products(const u32x4& a, const u32x4& b) {
                                                   0);
 }
 
-// Bound by vector issue (74 % of the SIMDs' cycles; 11.8K instructions a
+// Bound by vector issue (74 % of the SIMDs' cycles; 12.2K instructions a
 // packet at k = 8, uniform 1M: 47 chunks scanned, 63 boxes tested against the
-// queries, 113 queueing and 40 inserting steps).  One wave per workgroup, so
+// queries).  One wave per workgroup, so
 // that a slow packet holds no other's place; with five instead of four per
 // SIMD where the registers of short lists allow it without spills: the 1M call
 // 0.458 -> 0.411 ms.  Half-precision parts instead of
