@@ -50,15 +50,18 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // Pairs of chunks held in LDS until their candidates are inserted and the bounds
-// refreshed.  More fill the insertions better, which uniform points gain by; fewer
-// refresh sooner, which clusters gain by, and more: 2 for every list.  1M points
-// and queries, 4 -> 2, ms, uniform / mixture / clusters of many widths: 3-D, k = 1
-// 0.332 -> 0.332 / 0.410 -> 0.381 / 0.740 -> 0.677, k = 4 0.395 -> 0.397 / 0.547
-// -> 0.532 / 0.946 -> 0.880, k = 8 0.466 -> 0.474 / 0.668 -> 0.660 / 1.237 ->
-// 1.197, k = 32 1.473 -> 1.474 / 2.134 -> 2.106 / 3.436 -> 3.275; 4-D, k = 8 0.939
-// -> 0.955 / 1.160 -> 1.171 / 2.639 -> 2.570; 3-D, k = 8 from a model's radii 0.847
-// -> 0.813 / 1.772 -> 1.657; 300,000 queries of the uniform points 0.289 -> 0.301.
-constexpr int NPEND = 2;
+// refreshed: until a query has FLUSH candidates, but two at least and four at
+// most.  More pairs fill the insertions better, which few candidates (uniform
+// points) gain by; a sooner refresh spares the next chunks' candidates, which many
+// (clusters) gain by.  1M points and queries, always 4 / always 2 / by candidates,
+// ms: 3-D, k = 1 mixture 0.410 / 0.381 / 0.368, k = 8 uniform 0.466 / 0.474 / 0.467,
+// mixture 0.668 / 0.660 / 0.648, clusters of many widths 1.237 / 1.197 / 1.143, k =
+// 32 clusters 3.436 / 3.275 / 3.195, k = 8 from a model's radii, mixture 1.772 /
+// 1.657 / 1.600; 4-D, k = 8 uniform 0.939 / 0.955 / 0.935, clusters 2.639 / 2.570 /
+// 2.552, k = 16 uniform 1.328 / 1.349 / 1.317.  3 or 5 candidates instead of 4 are
+// within 1 % of it, 8 up to 2 % slower on clusters.
+constexpr uint32_t NPEND = 4;
+constexpr uint32_t FLUSH = 4;
 // Entry of the chunks held that a queue byte names.  Lanes without a candidate
 // read bytes that nothing wrote, so every byte has to name one of the entries.
 __host__ __device__ constexpr uint32_t held_entry(uint32_t byte, uint32_t entries) { return byte & (entries - 1u); }
@@ -254,7 +257,7 @@ __device__ __forceinline__ f32x16 products(const u32x4& a, const u32x4& b) {
                                                   0);
 }
 
-// Bound by vector issue (74 % of the SIMDs' cycles; 12.2K instructions a
+// Bound by vector issue (72 % of the SIMDs' cycles; 11.6K instructions a
 // packet at k = 8, uniform 1M: 47 chunks scanned, 63 boxes tested against the
 // queries).  One wave per workgroup, so
 // that a slow packet holds no other's place; with five instead of four per
@@ -738,7 +741,7 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 :
                 mask[c] = m.x | (m.y << 16);
             }
             ++npend;
-            const bool batch = npend == NPEND || last;
+            bool batch = npend == NPEND || last;
             uint64_t todo = uint64_t(mask[0]) | (uint64_t(mask[1]) << 32);
             for (;;) {
                 // every lane queues its candidates, until one lane's share is full
@@ -749,7 +752,8 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 :
                     if (wave_any(ncand == QCAP)) break;
                 }
                 const bool left = wave_any(todo != 0);
-                if (batch || left || wave_any(ncand == QCAP)) insert_queue();
+                batch = batch || left || (npend >= 2 && wave_any(ncand >= FLUSH));
+                if (batch || wave_any(ncand == QCAP)) insert_queue();
                 if (!left) break;
             }
             if (batch) {
