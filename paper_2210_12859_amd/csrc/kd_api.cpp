@@ -165,6 +165,18 @@ void pack_boxes(const float* pts, const int32_t* order, int64_t N, int D, std::v
     }
 }
 
+// kd_tree_s::fill of a tree packed on the host.
+template <int D>
+float fill_of(const std::vector<float>& boxes, int64_t N) {
+    if (N <= FILL_POINTS) return 0.0f;
+    constexpr int BW = box_words(D);
+    const float* root = &boxes[BW];
+    float sum = 0.0f;
+    for (int64_t i = int64_t(1) << FILL_LEVEL; i < int64_t(2) << FILL_LEVEL; ++i)
+        sum += box_share<D>(&boxes[i * BW], &boxes[i * BW] + BW / 2, root, root + BW / 2);
+    return sum;
+}
+
 kd_status build_from_host(const float* hp, int64_t N, int dim, kd_tree* out) {
     if (!out) return set_error(KD_EINVAL, "kd_build: out is NULL");
     if (N < 0 || N > KD_MAX_POINTS) return set_error(KD_EINVAL, "kd_build: N out of range [0, 2^30 - 1]");
@@ -212,6 +224,7 @@ kd_status build_from_host(const float* hp, int64_t N, int dim, kd_tree* out) {
             (void)hipFree(t->d_nodes);
             return set_error(KD_ENOMEM, "kd_build: host allocation");
         }
+        t->fill = dim == 2 ? fill_of<2>(boxes, N) : (dim == 3 ? fill_of<3>(boxes, N) : fill_of<4>(boxes, N));
         e = hipMalloc(&t->d_boxes, boxes.size() * 4);
         if (e == hipSuccess) e = hipMemcpy(t->d_boxes, boxes.data(), boxes.size() * 4, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
@@ -402,8 +415,9 @@ kd_status kd_build_ex(const float* points, int64_t N, int dim, int split, kd_str
         return KD_OK;
     }
     // read back in one copy: the order, then the root's box (the bounding box
-    // of all points), then the mark of a NaN or infinite coordinate
-    const size_t back = size_t(N) + 8 + 1;
+    // of all points), the mark of a NaN or infinite coordinate, the fill
+    const size_t back = size_t(N) + 8 + 1 + 1;
+    static_assert(ROOT_FILL == 9, "behind the mark");
     const bool widest = split == KD_SPLIT_WIDEST;
     // What the tree keeps is allocated before the workspace: the allocator then
     // hands both out again to the next build of the size (14 us each), while a
@@ -465,9 +479,10 @@ kd_status kd_build_ex(const float* points, int64_t N, int dim, int split, kd_str
     e = hipStreamSynchronize(st);
     if (s != KD_OK) return s;
     if (e != hipSuccess) return hip_error(e, "kd_build: read back");
-    if (t->order[back - 1] != 0) return set_error(KD_EINVAL, "kd_build: points contain NaN or inf");
+    if (t->order[size_t(N) + 8] != 0) return set_error(KD_EINVAL, "kd_build: points contain NaN or inf");
     float root_box[8];
     std::memcpy(root_box, t->order.data() + N, sizeof(root_box));
+    if (N > FILL_POINTS) std::memcpy(&t->fill, t->order.data() + N + ROOT_FILL, 4);
     t->order.resize(size_t(N));
     for (int j = 0; j < dim; ++j) {
         t->lo[j] = root_box[j];

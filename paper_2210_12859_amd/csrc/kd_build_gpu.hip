@@ -620,6 +620,33 @@ __global__ __launch_bounds__(512) void pack_levels(const float* __restrict__ pts
         }
         __syncthreads();
     }
+    if (lo == 0 && int64_t(N) > FILL_POINTS) {
+        // the boxes of FILL_LEVEL are this launch's or the one's before
+        float rl[D], rh[D], sum = 0.0f;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            rl[j] = lds[j][1];
+            rh[j] = lds[D + j][1];
+        }
+        for (uint32_t i = (1u << FILL_LEVEL) + threadIdx.x; i < (2u << FILL_LEVEL); i += 512) {
+            float l[D], h[D];
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                l[j] = hi > FILL_LEVEL ? lds[j][i] : boxes[size_t(i) * BW + j];
+                h[j] = hi > FILL_LEVEL ? lds[D + j][i] : boxes[size_t(i) * BW + HB + j];
+            }
+            sum += box_share<D>(l, h, rl, rh);
+        }
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) lds[0][threadIdx.x >> 6] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < 8; ++w) sum += lds[0][w];
+            root_box[ROOT_FILL] = sum;
+        }
+    }
 }
 
 inline dim3 grid_for(uint64_t n) { return dim3(unsigned((n + 255) / 256)); }

@@ -78,6 +78,23 @@ inline int32_t box_id_limit(int64_t N) {
 // query, or packets.
 enum class Route { lanes, wave, packets };
 
+// Evenness of a tree's points: the volumes of the subtree boxes of level
+// FILL_LEVEL over the root box's, summed (trees above FILL_POINTS).  0.97 to 0.98
+// for uniform points and grids, 0.8 to 0.9 for these with some clusters, below 0.5
+// for mixtures, normal clouds and shells.
+constexpr int FILL_LEVEL = 10;
+constexpr int64_t FILL_POINTS = 1 << 17;
+template <int D>
+__host__ __device__ inline float box_share(const float* lo, const float* hi, const float* root_lo,
+                                           const float* root_hi) {
+    float v = 1.0f;
+    for (int j = 0; j < D; ++j) {
+        const float ext = root_hi[j] - root_lo[j];
+        v *= ext > 0.0f ? (hi[j] - lo[j]) / ext : 1.0f;  // (no share in a flat dimension)
+    }
+    return v;
+}
+
 // Tuned launch parameters kept with a tree (filled by kd_autotune).
 struct TuneEntry {
     int k_template;  // compiled list size
@@ -98,6 +115,7 @@ struct kd_tree_s {
     int split = 0;                 // KD_SPLIT_LEVEL or KD_SPLIT_WIDEST
     float lo[4] = {0, 0, 0, 0};
     float hi[4] = {0, 0, 0, 0};
+    float fill = 0.0f;             // how much of the root's box the boxes of FILL_LEVEL fill (0: small trees)
     void* d_nodes = nullptr;       // node buffer: TreeRec<dim>[N + 2], record of node id i at index i
                                    // (+ int32 index[N + 2] when the record holds no index)
     void* d_boxes = nullptr;       // float[N + 2][box_words(dim)]: bounding box of the points of the
@@ -263,7 +281,9 @@ kd_status build_level_order_device(const float* d_pts, int64_t N, int dim, int32
 // with stored dimensions (d_pos_dims by position) the records' ancestor splits
 // follow them and d_dims (uint8 [N + 2], by node id) receives the packed
 // dimensions of each node and its three nearest ancestors.  root_box receives
-// the root's box_words(dim) words once more.
+// the root's box_words(dim) words once more, and at word ROOT_FILL the tree's
+// fill (see FILL_LEVEL; trees above FILL_POINTS).
+constexpr int ROOT_FILL = 9;
 kd_status pack_tree_device(const float* d_pts, const int32_t* d_order, int64_t N, int dim, void* d_nodes,
                            float* d_boxes, float* root_box, hipStream_t st, const uint8_t* d_pos_dims = nullptr,
                            uint8_t* d_dims = nullptr);

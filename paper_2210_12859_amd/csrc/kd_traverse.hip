@@ -1608,7 +1608,22 @@ Route call_route(kd_tree t, int K, int64_t Q, bool lanes_only, bool model) {
     if (!model && Q <= wave_queries(t->dim, K)) return Route::wave;
     // without a first walk sparse queries cost more (2M points, 300,000 queries,
     // k = 8: 0.34 lane by lane, 0.53 ms)
-    return use_packets(t, K, Q) && (!model || Q >= t->N / 2) ? Route::packets : Route::lanes;
+    if (!use_packets(t, K, Q) || (model && Q < t->N / 2)) return Route::lanes;
+    // Over evenly spread points the lanes' walks are short and alike, and packets
+    // pay later: once there are enough to fill the GPU, and the more the sparser the
+    // queries and the shorter the lists.  Uniform 3-D, lane by lane / packets at and
+    // the worst below the line: k = 1, 2M points 0.97 (500,000 queries 0.86, 200,000
+    // 0.47), 500,000 1.17; k = 4, 1M 1.09 (400,000: 0.95), 4M 1.04; k = 8, 300,000
+    // points and queries 1.06 (200,000 each: 0.88), 1M and 400,000 0.99 (200,000:
+    // 0.71), 4M and 700,000 1.01, 8M and 1.5M 1.37; k = 32, 1M 1.08, 4M 1.0; 4-D, k =
+    // 8, 1M and 400,000 1.11 (200,000: 0.84), 4M and 700,000 1.11.  (Mixtures: 1M and
+    // 220,000, k = 8: 2.7; none below 0.97 at the lines of use_packets.)
+    if (t->fill > 0.7f) {
+        const int wide = t->dim - 2;
+        const int part = K == 1 ? wide : (K == 2 ? 2 * wide : (K == 4 || K == 32 ? 4 * wide : 8));
+        if (Q < 250000 + t->N / part) return Route::lanes;
+    }
+    return Route::packets;
 }
 
 kd_status run_batch_packets(const BatchJob* d_jobs, int njobs, int dim, int K, uint32_t n, uint32_t packets,
