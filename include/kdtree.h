@@ -370,7 +370,9 @@ kd_status kd_radius_model_train(kd_tree t, const float* train_q, int64_t Qt, int
  * the whole tree.  visited (nullable, device uint32 [Q]) counts processed
  * nodes of both runs; stats (nullable, HOST) receives the counts and stage
  * times above (radius_ms includes the start-node descent), which
- * synchronises the stream. */
+ * synchronises the stream.  Without visited and stats, a call that kd_knn
+ * answers with another kernel than the lanes (see kd_opts) takes it here too:
+ * rows do not depend on the radius, and these kernels gain nothing by it. */
 kd_status kd_knn_learned(kd_tree t, kd_model m, const float* queries, int64_t Q, int k, float maxRadius,
                          int32_t* out_idx, float* out_d2, uint32_t* visited, kd_stats* stats, const kd_opts* opts,
                          kd_stream stream);

@@ -359,7 +359,7 @@ kd_status knn_entry(kd_tree t, const float* queries, int64_t Q, int k, float max
     kd_status s = check_query_args(t, queries, Q, k, maxRadius, out_idx, fn);
     if (s != KD_OK) return s;
     QueryPlan plan;
-    s = resolve_plan(t, k, maxRadius, opts, Q, call_route(t, k_template(k), Q, visited != nullptr, false), plan);
+    s = resolve_plan(t, k, maxRadius, opts, Q, call_route(t, k_template(k), Q, visited != nullptr), plan);
     if (s != KD_OK) return s;
     if (Q == 0) return KD_OK;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);

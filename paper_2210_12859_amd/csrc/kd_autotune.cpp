@@ -91,7 +91,7 @@ kd_status kd_autotune(kd_tree t, const float* sample_q, int64_t Qs, int k, float
     }
     float best = INFINITY, best_lanes = INFINITY;
     kd_opts bo = cands.front(), bl = cands.front();
-    const Route route = call_route(t, K, Qs, false, false);
+    const Route route = call_route(t, K, Qs, false);
     uint64_t ref = 0;
     bool have_ref = false;
     for (const kd_opts& o : cands) {

@@ -187,9 +187,8 @@ struct QueryPlan {
 };
 int k_template(int k);
 // The route of a kNN call (kd_traverse.hip).  lanes_only: it asks for what the
-// lanes alone give (visited nodes, statistics, the caller's radii); model: its
-// radii come from a model.
-Route call_route(kd_tree t, int K, int64_t Q, bool lanes_only, bool model);
+// lanes alone give (visited nodes, statistics, the caller's radii).
+Route call_route(kd_tree t, int K, int64_t Q, bool lanes_only);
 
 // One job of a batched call, as the device sees it.  Jobs of one (dim, K)
 // class are laid out back to back in a class slot space.
@@ -307,7 +306,6 @@ struct FixedScratch {
 // the k-th squared distance each) and counted in *fb_count (zero at launch).
 struct PacketCall {
     const void* sq;  // NodeRec<dim>[Q], sorted
-    const float* w0; // initial squared radii by sorted place, or NULL
     uint32_t Q;
     int k;
     float R2;

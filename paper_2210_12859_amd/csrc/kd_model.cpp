@@ -320,7 +320,7 @@ kd_status kd_knn_learned(kd_tree t, kd_model m, const float* queries, int64_t Q,
         return knn_entry(t, queries, Q, k, maxRadius, out_idx, out_d2, visited, opts, stream, "kd_knn_learned");
     QueryPlan plan;
     s = resolve_plan_public(t, k, maxRadius, opts, Q,
-                            call_route(t, k_template(k), Q, visited != nullptr || stats != nullptr, true), plan);
+                            call_route(t, k_template(k), Q, visited != nullptr || stats != nullptr), plan);
     if (s != KD_OK) return s;
     LearnedSpec ls{};
     ls.params = m->d_params;

@@ -73,7 +73,6 @@ constexpr bool held_entries_hold(uint32_t entries) {
 static_assert(held_entries_hold(NPEND * 64), "queue bytes");
 constexpr int QCAP = 16;        // candidates a query can hold until then
 constexpr uint32_t MAX_HOME = 8;          // chunk pairs of the first walk
-constexpr int SHORT_LISTS = 8;            // lists left short by initial radii that repeat a packet
 constexpr uint32_t NO_KEY = 0x7fe00000u;  // high word above every key's
 // scaled |p'|^2 of an empty slot: never a candidate, as the query side of the
 // product is at least -2 |p'| |q'| - r^2 - slack > -2 240 64 - 4200
@@ -87,7 +86,6 @@ struct PacketArgs {
     int32_t N;
     GroupShape shape;
     const void* sq;          // NodeRec<D>[Q], sorted
-    const float* w0;         // initial squared radii (they may hold fewer than k points), or NULL
     uint32_t Q;
     int k;
     float R2;
@@ -267,9 +265,9 @@ __device__ __forceinline__ f32x16 products(const u32x4& a, const u32x4& b) {
 // a chunk.  Lists over 32 are left to the other kernels: the allocator would
 // copy live registers inside divergent regions, which loses them in the
 // inactive lanes.
-// Where a packet's queries come from: one call's sorted records, the same with
-// initial radii, or the class slots of jobs.
-enum Source { CALL, RADII, JOBS };
+// Where a packet's queries come from: one call's sorted records, or the class
+// slots of jobs.
+enum Source { CALL, JOBS };
 template <int D, int K, Source SRC>
 __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 : 5) : 1) void knn_packet(PacketArgs a) {
     __shared__ float4 pt[NPEND * 64];                    // points of the chunks held
@@ -539,267 +537,238 @@ __global__ __launch_bounds__(64, K <= 8 ? (D == 4 || K <= 2 || SRC != CALL ? 4 :
         }
     };
 
-    // With initial radii the second walk starts from them.  If they reach too
-    // many leaves or leave SHORT_LISTS lists short, it starts over from bounds of
-    // its own; fewer short lists are searched again from R2 by the
-    // one-wave-per-query kernel.  500,000 uniform 3-D points, 700,001 queries, k =
-    // 8, lane by lane / here, ms, for true k-th distances times 0.98: 0.88 / 0.61,
-    // 1.02: 0.47 / 0.28, 1.3: 0.50 / 0.33 (0.43 without radii).
     float worst = a.R2;
-    bool bounded = true;
-    if constexpr (SRC == RADII) {
-        worst = fminf(worst, a.w0[have ? slot : first]);
-        bounded = wave_any(s.active & !(worst <= COORD_MAX));
-    }
     uint64_t L[K];
     uint32_t leaves = 0;
     bool over = false;
-    for (;;) {
-        // ---- first walk: an upper bound of every query's k-th distance
-        if (bounded) {
-            worst = a.R2;
-            // Short lists take one result for every 2 RUN points, the smallest: this
-            // loosens the bound little where few of the points are among the k
-            // nearest, and cannot tighten it.  fcp, 1M uniform / mixture points: 0.318
-            // -> 0.302 / 0.462 -> 0.451 ms with RUN 4 instead of 1; k = 8 with RUN 2:
-            // 0.472 -> 0.486, with 4: 0.585 ms.
-            constexpr int RUN = K <= 2 ? 4 : 1;
-            float F[K];
+    // ---- first walk: an upper bound of every query's k-th distance
+    {
+        // Short lists take one result for every 2 RUN points, the smallest: this
+        // loosens the bound little where few of the points are among the k
+        // nearest, and cannot tighten it.  fcp, 1M uniform / mixture points: 0.318
+        // -> 0.302 / 0.462 -> 0.451 ms with RUN 4 instead of 1; k = 8 with RUN 2:
+        // 0.472 -> 0.486, with 4: 0.585 ms.
+        constexpr int RUN = K <= 2 ? 4 : 1;
+        float F[K];
 #pragma unroll
-            for (int j = 0; j < K; ++j) F[j] = j < K - a.k ? -PT_NONE : PT_NONE;
-            uint32_t seen = 0;
-            bool scaled = false;
-            // scale of the first leaves found: their boxes and the queries within
-            // half of COORD_CLAMP (points of later leaves beyond it are left out)
-            auto set_scale = [&](float extent) {
-                const float e = fmaxf(extent, qmax);
-                s.set_query(0.5f * COORD_CLAMP / fmaxf(e, 1.0e-15f));
-                s.set_threshold(0.0f);
-                scaled = true;
-            };
-            auto insert = [&](float x) {
-                if (K <= 8 || wave_any(x < F[K - 1])) {
-#pragma unroll
-                    for (int j = K - 1; j > 0; --j) F[j] = __builtin_amdgcn_fmed3f(F[j - 1], x, F[j]);
-                    F[0] = fminf(F[0], x);
-                }
-            };
-            auto bound_chunks = [&](const Chunks& ch, bool) {
-                ++seen;
-                u32x4 pa[2];
-                s.template point_operands<true>(ch.p, ch.ok, pa[0], pa[1]);
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const f32x16 acc_lo = products(pa[c], s.b_lo), acc_hi = products(pa[c], s.b_hi);
-#pragma unroll
-                    for (int i = 0; i < 16; i += RUN) {
-                        float lo = acc_lo[i], hi = acc_hi[i];
-#pragma unroll
-                        for (int e = 1; e < RUN; ++e) {
-                            lo = fminf(lo, acc_lo[i + e]);
-                            hi = fminf(hi, acc_hi[i + e]);
-                        }
-                        // both halves' results of the lane's own query
-                        const u32x2 v = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi),
-                                                                         false, false);
-                        if (K <= 8) {
-                            insert(fminf(__uint_as_float(v.x), __uint_as_float(v.y)));
-                        } else {
-                            insert(__uint_as_float(v.x));
-                            insert(__uint_as_float(v.y));
-                        }
-                    }
-                }
-            };
-            auto expand_home = [&](int32_t r, int32_t lv, bool to_leaves) -> uint32_t {
-                const float gap = child_gap(r, lv);
-                uint64_t m = wave_ballot(gap <= 0.0f);
-                uint32_t out;
-                if (m) {
-                    const uint32_t all = uint32_t(m) | uint32_t(m >> 32);
-                    const uint32_t in = test_children(all, 0.0f);
-                    out = in ? in : all;
-                } else {
-                    // no child overlaps the packet: the nearest one
-                    const float best = -both_halves_max(half_max(-gap));
-                    m = wave_ballot(gap == best);
-                    m &= ~(m - 1);
-                    out = uint32_t(m) | uint32_t(m >> 32);
-                }
-                if (to_leaves) {
-                    // a leaf holds 15 points or more: with longer lists its
-                    // sibling, then its cousins come along
-                    if (K > 8) out |= (out & 0x55555555u) << 1 | (out & 0xaaaaaaaau) >> 1;
-                    if (K > 16) out |= (out & 0x33333333u) << 2 | (out & 0xccccccccu) >> 2;
-                    if (lv < GL) out &= (1u << (1 << lv)) - 1u;
-                    for (uint32_t rest = out; rest && nhome < 32; rest &= rest - 1, ++nhome)
-                        home = lane == nhome ? (r << lv) + int32_t(__builtin_ctz(rest)) : home;
-                    if (!scaled) {
-                        float e = 0.0f;
-#pragma unroll
-                        for (int j = 0; j < D; ++j) e = fmaxf(e, fmaxf(fabsf(bl[j] - s.c[j]), fabsf(bh[j] - s.c[j])));
-                        const bool mine = (out >> (lane & 31u)) & 1u;
-                        set_scale(both_halves_max(half_max(mine ? e : 0.0f)));
-                    }
-                }
-                return out;
-            };
-            if (a.shape.leaf_group == 0) {
-                float e = 0.0f;
-#pragma unroll
-                for (int j = 0; j < D; ++j) {
-                    const float* b = a.boxes + box_words(D);
-                    e = fmaxf(e, fmaxf(fabsf(b[j] - s.c[j]), fabsf(b[box_words(D) / 2 + j] - s.c[j])));
-                }
-                set_scale(e);
-            }
-            walk(0, false, expand_home, bound_chunks, [&]() { return seen >= MAX_HOME; });
-            // back from scaled units; the last terms cover the rounding and
-            // underflow of that
-            const float d = fmaxf(F[K - 1] + s.qq, 0.0f);
-            const float inv = 1.0f / s.scale;
-            const float b = (d + packet_slack(s.qn, __builtin_amdgcn_sqrtf(d) + 0.02f)) * inv * inv * 1.00001f + 1.0e-37f;
-            worst = F[K - 1] < BOUND_MAX ? fminf(worst, b) : worst;
-        }
-        // queries that found too few points to be bounded are left over
-        {
-            const bool open = s.active & !(worst <= COORD_MAX);
-            hand_over(open, a.R2);
-            s.active = s.active & !open;
-            if (!wave_any(s.active)) return;
-            worst = s.active ? worst : 0.0f;
-        }
-
-        // ---- second walk: every group within the bounds
-        {
-            const uint64_t sent = make_key(worst, SENT_IDX);
-#pragma unroll
-            for (int j = 0; j < K; ++j) L[j] = j < K - a.k ? uint64_t(0) : sent;
-        }
-        {
-            const float reach = s.active ? qlen + __builtin_amdgcn_sqrtf(worst) : 0.0f;
-            s.set_query(PACKET_SCALE / fmaxf(1.001f * both_halves_max(half_max(reach)), 1.0e-15f));
-        }
-        auto refresh = [&]() {
-            worst = key_d2(L[K - 1]);
-            const float r = __builtin_amdgcn_sqrtf(worst) * s.scale;
-            s.set_threshold(s.qq - r * r - packet_slack(s.qn, r));
+        for (int j = 0; j < K; ++j) F[j] = j < K - a.k ? -PT_NONE : PT_NONE;
+        uint32_t seen = 0;
+        bool scaled = false;
+        // scale of the first leaves found: their boxes and the queries within
+        // half of COORD_CLAMP (points of later leaves beyond it are left out)
+        auto set_scale = [&](float extent) {
+            const float e = fmaxf(extent, qmax);
+            s.set_query(0.5f * COORD_CLAMP / fmaxf(e, 1.0e-15f));
+            s.set_threshold(0.0f);
+            scaled = true;
         };
-        refresh();
-        uint32_t ncand = 0;  // candidates of the lane's query in the queue
-        uint32_t npend = 0;  // chunks held
-        auto insert_queue = [&]() {
-            // every lane takes its next candidates, two at a time; lanes without
-            // one read some held point and insert the largest key, which changes
-            // nothing
-            auto key_at = [&](uint32_t i) -> uint64_t {
-                const uint32_t at = held_entry(queue[i * 64u + lane], NPEND * 64u);
-                const float4 w = pt[at];
-                float p[D];
-                p[0] = w.x;
-                p[1] = w.y;
-                p[2] = w.z;
-                if (D > 3) p[D > 3 ? 3 : 0] = w.w;
-                const float dx0 = s.q[0] - p[0];
-                float d2 = dx0 * dx0;
+        auto insert = [&](float x) {
+            if (K <= 8 || wave_any(x < F[K - 1])) {
 #pragma unroll
-                for (int j = 1; j < D; ++j) {
-                    const float dx = s.q[j] - p[j];
-                    d2 = d2 + dx * dx;
-                }
-                const int32_t idx = D == 3 ? __float_as_int(w.w) : pid[at];
-                return (uint64_t(i < ncand ? __float_as_uint(d2) : NO_KEY) << 32) | uint32_t(idx);
-            };
-            for (uint32_t i = 0; wave_any(i < ncand); i += 2) {
-                const uint64_t k0 = key_at(i), k1 = key_at(i + 1);
-                list_insert<K>(L, k0);
-                list_insert<K>(L, k1);
+                for (int j = K - 1; j > 0; --j) F[j] = __builtin_amdgcn_fmed3f(F[j - 1], x, F[j]);
+                F[0] = fminf(F[0], x);
             }
-            ncand = 0;
         };
-        auto scan_chunks = [&](const Chunks& ch, bool last) {
-            const uint32_t base = npend * 64u;
-            lds_order();  // other lanes read the entries held before
-            {
-                const uint32_t at = base + (lane & 32u) + uint32_t(s.slot);
-                float4 w;
-                w.x = ch.p[0];
-                w.y = ch.p[1];
-                w.z = ch.p[2];
-                w.w = D == 3 ? __int_as_float(ch.idx) : (D == 4 ? ch.p[D > 3 ? 3 : 0] : 0.0f);
-                pt[at] = w;
-                if (D == 4) pid[at] = ch.idx;
-            }
-            lds_order();
+        auto bound_chunks = [&](const Chunks& ch, bool) {
+            ++seen;
             u32x4 pa[2];
-            s.template point_operands<false>(ch.p, ch.ok, pa[0], pa[1]);
-            uint32_t mask[2];
+            s.template point_operands<true>(ch.p, ch.ok, pa[0], pa[1]);
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
-                const uint32_t m_lo = sign_bits(products(pa[c], s.b_lo)), m_hi = sign_bits(products(pa[c], s.b_hi));
-                const u32x2 m = __builtin_amdgcn_permlane32_swap(m_lo, m_hi, false, false);
-                mask[c] = m.x | (m.y << 16);
-            }
-            ++npend;
-            bool batch = npend == NPEND || last;
-            uint64_t todo = uint64_t(mask[0]) | (uint64_t(mask[1]) << 32);
-            for (;;) {
-                // every lane queues its candidates, until one lane's share is full
-                while (wave_any(todo != 0)) {
-                    queue[ncand * 64u + lane] = uint8_t(base + first_bit(todo));
-                    ncand += todo != 0 ? 1u : 0u;
-                    todo &= todo - 1;
-                    if (wave_any(ncand == QCAP)) break;
+                const f32x16 acc_lo = products(pa[c], s.b_lo), acc_hi = products(pa[c], s.b_hi);
+#pragma unroll
+                for (int i = 0; i < 16; i += RUN) {
+                    float lo = acc_lo[i], hi = acc_hi[i];
+#pragma unroll
+                    for (int e = 1; e < RUN; ++e) {
+                        lo = fminf(lo, acc_lo[i + e]);
+                        hi = fminf(hi, acc_hi[i + e]);
+                    }
+                    // both halves' results of the lane's own query
+                    const u32x2 v = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi),
+                                                                     false, false);
+                    if (K <= 8) {
+                        insert(fminf(__uint_as_float(v.x), __uint_as_float(v.y)));
+                    } else {
+                        insert(__uint_as_float(v.x));
+                        insert(__uint_as_float(v.y));
+                    }
                 }
-                const bool left = wave_any(todo != 0);
-                batch = batch || left || (npend >= 2 && wave_any(ncand >= FLUSH));
-                if (batch || wave_any(ncand == QCAP)) insert_queue();
-                if (!left) break;
-            }
-            if (batch) {
-                npend = 0;
-                refresh();
             }
         };
-        auto expand_in = [&](int32_t r, int32_t lv, bool to_leaves) -> uint32_t {
+        auto expand_home = [&](int32_t r, int32_t lv, bool to_leaves) -> uint32_t {
             const float gap = child_gap(r, lv);
-            const uint64_t m = wave_ballot(gap <= half_max(worst));
-            uint32_t mm = uint32_t(m) | uint32_t(m >> 32);
+            uint64_t m = wave_ballot(gap <= 0.0f);
+            uint32_t out;
+            if (m) {
+                const uint32_t all = uint32_t(m) | uint32_t(m >> 32);
+                const uint32_t in = test_children(all, 0.0f);
+                out = in ? in : all;
+            } else {
+                // no child overlaps the packet: the nearest one
+                const float best = -both_halves_max(half_max(-gap));
+                m = wave_ballot(gap == best);
+                m &= ~(m - 1);
+                out = uint32_t(m) | uint32_t(m >> 32);
+            }
             if (to_leaves) {
-                // leaves already taken
-                for (uint32_t i = 0; i < nhome; ++i) {
-                    const uint32_t off = __builtin_amdgcn_readlane(uint32_t(home), i) - uint32_t(r << lv);
-                    mm &= off < 32u ? ~(1u << off) : ~0u;
+                // a leaf holds 15 points or more: with longer lists its
+                // sibling, then its cousins come along
+                if (K > 8) out |= (out & 0x55555555u) << 1 | (out & 0xaaaaaaaau) >> 1;
+                if (K > 16) out |= (out & 0x33333333u) << 2 | (out & 0xccccccccu) >> 2;
+                if (lv < GL) out &= (1u << (1 << lv)) - 1u;
+                for (uint32_t rest = out; rest && nhome < 32; rest &= rest - 1, ++nhome)
+                    home = lane == nhome ? (r << lv) + int32_t(__builtin_ctz(rest)) : home;
+                if (!scaled) {
+                    float e = 0.0f;
+#pragma unroll
+                    for (int j = 0; j < D; ++j) e = fmaxf(e, fmaxf(fabsf(bl[j] - s.c[j]), fabsf(bh[j] - s.c[j])));
+                    const bool mine = (out >> (lane & 31u)) & 1u;
+                    set_scale(both_halves_max(half_max(mine ? e : 0.0f)));
                 }
             }
-            const uint32_t in = test_children(mm, worst);
-            if (to_leaves) {
-                leaves += uint32_t(__popc(in));
-                over = leaves > a.leaf_limit;
-                if (over) return 0;
-            }
-            return in;
+            return out;
         };
-        walk(nhome, true, expand_in, scan_chunks, [&]() { return over; });
-        if (over && bounded) {
-            hand_over(s.active, worst);
-            return;
-        }
-        if constexpr (SRC == RADII) {
-            const bool is_short = s.active & (uint32_t(L[K - 1]) == SENT_IDX) & (key_d2(L[K - 1]) < a.R2);
-            const bool again = !bounded && (over || __popcll(wave_ballot(is_short)) >= SHORT_LISTS);
-            if (!again) {
-                if (bounded) break;
-                hand_over(is_short, a.R2);
-                s.active = s.active & !is_short;
-                break;
+        if (a.shape.leaf_group == 0) {
+            float e = 0.0f;
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                const float* b = a.boxes + box_words(D);
+                e = fmaxf(e, fmaxf(fabsf(b[j] - s.c[j]), fabsf(b[box_words(D) / 2 + j] - s.c[j])));
             }
-            bounded = true;
-            over = false;
-            leaves = 0;
-        } else {
-            break;
+            set_scale(e);
         }
+        walk(0, false, expand_home, bound_chunks, [&]() { return seen >= MAX_HOME; });
+        // back from scaled units; the last terms cover the rounding and
+        // underflow of that
+        const float d = fmaxf(F[K - 1] + s.qq, 0.0f);
+        const float inv = 1.0f / s.scale;
+        const float b = (d + packet_slack(s.qn, __builtin_amdgcn_sqrtf(d) + 0.02f)) * inv * inv * 1.00001f + 1.0e-37f;
+        worst = F[K - 1] < BOUND_MAX ? fminf(worst, b) : worst;
+    }
+    // queries that found too few points to be bounded are left over
+    {
+        const bool open = s.active & !(worst <= COORD_MAX);
+        hand_over(open, a.R2);
+        s.active = s.active & !open;
+        if (!wave_any(s.active)) return;
+        worst = s.active ? worst : 0.0f;
+    }
+
+    // ---- second walk: every group within the bounds
+    {
+        const uint64_t sent = make_key(worst, SENT_IDX);
+#pragma unroll
+        for (int j = 0; j < K; ++j) L[j] = j < K - a.k ? uint64_t(0) : sent;
+    }
+    {
+        const float reach = s.active ? qlen + __builtin_amdgcn_sqrtf(worst) : 0.0f;
+        s.set_query(PACKET_SCALE / fmaxf(1.001f * both_halves_max(half_max(reach)), 1.0e-15f));
+    }
+    auto refresh = [&]() {
+        worst = key_d2(L[K - 1]);
+        const float r = __builtin_amdgcn_sqrtf(worst) * s.scale;
+        s.set_threshold(s.qq - r * r - packet_slack(s.qn, r));
+    };
+    refresh();
+    uint32_t ncand = 0;  // candidates of the lane's query in the queue
+    uint32_t npend = 0;  // chunks held
+    auto insert_queue = [&]() {
+        // every lane takes its next candidates, two at a time; lanes without
+        // one read some held point and insert the largest key, which changes
+        // nothing
+        auto key_at = [&](uint32_t i) -> uint64_t {
+            const uint32_t at = held_entry(queue[i * 64u + lane], NPEND * 64u);
+            const float4 w = pt[at];
+            float p[D];
+            p[0] = w.x;
+            p[1] = w.y;
+            p[2] = w.z;
+            if (D > 3) p[D > 3 ? 3 : 0] = w.w;
+            const float dx0 = s.q[0] - p[0];
+            float d2 = dx0 * dx0;
+#pragma unroll
+            for (int j = 1; j < D; ++j) {
+                const float dx = s.q[j] - p[j];
+                d2 = d2 + dx * dx;
+            }
+            const int32_t idx = D == 3 ? __float_as_int(w.w) : pid[at];
+            return (uint64_t(i < ncand ? __float_as_uint(d2) : NO_KEY) << 32) | uint32_t(idx);
+        };
+        for (uint32_t i = 0; wave_any(i < ncand); i += 2) {
+            const uint64_t k0 = key_at(i), k1 = key_at(i + 1);
+            list_insert<K>(L, k0);
+            list_insert<K>(L, k1);
+        }
+        ncand = 0;
+    };
+    auto scan_chunks = [&](const Chunks& ch, bool last) {
+        const uint32_t base = npend * 64u;
+        lds_order();  // other lanes read the entries held before
+        {
+            const uint32_t at = base + (lane & 32u) + uint32_t(s.slot);
+            float4 w;
+            w.x = ch.p[0];
+            w.y = ch.p[1];
+            w.z = ch.p[2];
+            w.w = D == 3 ? __int_as_float(ch.idx) : (D == 4 ? ch.p[D > 3 ? 3 : 0] : 0.0f);
+            pt[at] = w;
+            if (D == 4) pid[at] = ch.idx;
+        }
+        lds_order();
+        u32x4 pa[2];
+        s.template point_operands<false>(ch.p, ch.ok, pa[0], pa[1]);
+        uint32_t mask[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const uint32_t m_lo = sign_bits(products(pa[c], s.b_lo)), m_hi = sign_bits(products(pa[c], s.b_hi));
+            const u32x2 m = __builtin_amdgcn_permlane32_swap(m_lo, m_hi, false, false);
+            mask[c] = m.x | (m.y << 16);
+        }
+        ++npend;
+        bool batch = npend == NPEND || last;
+        uint64_t todo = uint64_t(mask[0]) | (uint64_t(mask[1]) << 32);
+        for (;;) {
+            // every lane queues its candidates, until one lane's share is full
+            while (wave_any(todo != 0)) {
+                queue[ncand * 64u + lane] = uint8_t(base + first_bit(todo));
+                ncand += todo != 0 ? 1u : 0u;
+                todo &= todo - 1;
+                if (wave_any(ncand == QCAP)) break;
+            }
+            const bool left = wave_any(todo != 0);
+            batch = batch || left || (npend >= 2 && wave_any(ncand >= FLUSH));
+            if (batch || wave_any(ncand == QCAP)) insert_queue();
+            if (!left) break;
+        }
+        if (batch) {
+            npend = 0;
+            refresh();
+        }
+    };
+    auto expand_in = [&](int32_t r, int32_t lv, bool to_leaves) -> uint32_t {
+        const float gap = child_gap(r, lv);
+        const uint64_t m = wave_ballot(gap <= half_max(worst));
+        uint32_t mm = uint32_t(m) | uint32_t(m >> 32);
+        if (to_leaves) {
+            // leaves already taken
+            for (uint32_t i = 0; i < nhome; ++i) {
+                const uint32_t off = __builtin_amdgcn_readlane(uint32_t(home), i) - uint32_t(r << lv);
+                mm &= off < 32u ? ~(1u << off) : ~0u;
+            }
+        }
+        const uint32_t in = test_children(mm, worst);
+        if (to_leaves) {
+            leaves += uint32_t(__popc(in));
+            over = leaves > a.leaf_limit;
+            if (over) return 0;
+        }
+        return in;
+    };
+    walk(nhome, true, expand_in, scan_chunks, [&]() { return over; });
+    if (over) {
+        hand_over(s.active, worst);
+        return;
     }
     // results
     if (!s.active) return;
@@ -880,7 +849,6 @@ hipError_t launch_knn_packet(kd_tree t, int K, const PacketCall& c, hipStream_t 
     a.N = int32_t(t->N);
     a.shape = group_shape(t->N);
     a.sq = c.sq;
-    a.w0 = c.w0;
     a.Q = c.Q;
     a.k = c.k;
     a.R2 = c.R2;
@@ -893,8 +861,8 @@ hipError_t launch_knn_packet(kd_tree t, int K, const PacketCall& c, hipStream_t 
     a.fb_w0 = c.fb_w0;
     const int64_t packets = (int64_t(c.Q) + 63) / 64;
     switch (t->dim) {
-        case 3: return a.w0 ? launch_packet_k<3, RADII>(K, a, packets, st) : launch_packet_k<3, CALL>(K, a, packets, st);
-        case 4: return a.w0 ? launch_packet_k<4, RADII>(K, a, packets, st) : launch_packet_k<4, CALL>(K, a, packets, st);
+        case 3: return launch_packet_k<3, CALL>(K, a, packets, st);
+        case 4: return launch_packet_k<4, CALL>(K, a, packets, st);
     }
     return hipErrorInvalidValue;
 }

@@ -1603,12 +1603,10 @@ bool batch_by_wave(int dim, int K, int64_t n) { return n <= std::min(wave_querie
 
 bool batch_packet_job(kd_tree t, int K, int64_t Q) { return use_packets(t, K, Q); }
 
-Route call_route(kd_tree t, int K, int64_t Q, bool lanes_only, bool model) {
+Route call_route(kd_tree t, int K, int64_t Q, bool lanes_only) {
     if (lanes_only || t->N == 0 || Q == 0) return Route::lanes;
-    if (!model && Q <= wave_queries(t->dim, K)) return Route::wave;
-    // without a first walk sparse queries cost more (2M points, 300,000 queries,
-    // k = 8: 0.34 lane by lane, 0.53 ms)
-    if (!use_packets(t, K, Q) || (model && Q < t->N / 2)) return Route::lanes;
+    if (Q <= wave_queries(t->dim, K)) return Route::wave;
+    if (!use_packets(t, K, Q)) return Route::lanes;
     // Over evenly spread points the lanes' walks are short and alike, and packets
     // pay later: once there are enough to fill the GPU, and the more the sparser the
     // queries and the shorter the lists.  Uniform 3-D, lane by lane / packets at and
@@ -1679,13 +1677,16 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
     const int heavy_trips = plan.heavy_default && use_boxes ? KD_DEFAULT_HEAVY_TRIPS_BOXES : plan.heavy_trips;
     const bool handoff = heavy_trips > 0 && visited == nullptr;
     kd_status s = KD_OK;
+    const Route route =
+        plan.plain ? call_route(t, plan.K, Q, visited || stats || (learned && !learned->params)) : Route::lanes;
+    // Rows do not depend on a model's radii, and the other kernels find better
+    // bounds in less time than the model takes: 500,000 uniform 3-D points, 700,001
+    // queries, packets from the model's radii 0.385, without 0.352 ms (lane by lane
+    // 0.58); 1M mixture points and queries, k = 8 1.49 and 0.65, k = 20 4.60 and 1.51
+    // (2.88).  Caller radii, which come with flags, and counts of restarts keep the
+    // lanes.
+    if (route != Route::lanes) learned = nullptr;
     // few queries: one wave each (no scratch, one launch)
-    // radii from a model suit packets as queries do, those of the caller may be
-    // anything (three times too large: lane by lane 0.52, packets 0.72 ms) and
-    // keep the lanes, as do counts of restarts
-    const Route route = plan.plain ? call_route(t, plan.K, Q, visited || stats || (learned && !learned->params),
-                                                learned != nullptr)
-                                   : Route::lanes;
     const bool by_wave = route == Route::wave, packet = route == Route::packets;
     if (by_wave && Q <= WAVE_UNSORTED) {
         hipEvent_t ev = nullptr;
@@ -1773,7 +1774,7 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
         else
             e = launch_radius_to_worst0(t->dim, learned->r0, sq, uint32_t(Q), plan.R2, worst0, st);
         if (e != hipSuccess) return hip_error(e, "initial radius launch");
-        if (!packet) e = launch_learned_start(t->dim, t->d_nodes, int32_t(t->N), sq, worst0, uint32_t(Q), start, st);
+        e = launch_learned_start(t->dim, t->d_nodes, int32_t(t->N), sq, worst0, uint32_t(Q), start, st);
         if (e != hipSuccess) return hip_error(e, "start node launch");
         s = timing_end(st, evm, "mlp");
         if (s != KD_OK) return s;
@@ -1826,7 +1827,6 @@ kd_status run_knn(kd_tree t, const float* queries, int64_t Q, const QueryPlan& p
             char* w = static_cast<char*>(sort_ws);
             PacketCall pc = {};
             pc.sq = sq;
-            pc.w0 = worst0;
             pc.Q = uint32_t(Q);
             pc.k = plan.k;
             pc.R2 = plan.R2;

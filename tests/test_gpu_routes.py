@@ -134,3 +134,32 @@ def test_batch_options_make_the_kept_plan_again():
     again.run()
     torch.cuda.synchronize()
     assert all(torch.equal(j["out_idx"], r) for j, r in zip(jobs, rows))
+
+
+@pytest.mark.parametrize("q,stats", [(300, False), (300, True), (120_000, False), (400_000, False), (400_000, True)])
+def test_models_cost_nothing_where_rows_do_not_need_them(oracle_lib, q, stats):
+    """Calls with a model take the kernels of kd_knn; the model runs where
+    statistics ask for it, or the call goes lane by lane (120,000 queries over 1M
+    points)."""
+    import paper_2210_12859_amd as kd
+    rng = np.random.default_rng(q)
+    n = 1_000_000 if q == 120_000 else 300_000
+    P, Qs = _data(rng, n, 3), _data(rng, q, 3)
+    g = torch.from_numpy(Qs).to("cuda:0")
+    tree = kd.kd_build(torch.from_numpy(P).to("cuda:0"))
+    model = kd.kd_radius_model_train(tree, torch.from_numpy(_data(rng, 4096, 3)).to("cuda:0"), 8, epochs=1)
+    print(f"[gpu] model route q={q} stats={stats}", flush=True)
+    kd.kd_timing_enable(True)
+    try:
+        kd.kd_timing_collect("mlp")
+        i, d = kd.kd_knn_learned(tree, model, g, 8, want_stats=stats)[:2]
+        torch.cuda.synchronize()
+        runs = kd.kd_timing_collect("mlp")[1]
+        for stage in ("sort", "traverse"):
+            kd.kd_timing_collect(stage)
+    finally:
+        kd.kd_timing_enable(False)
+    assert (runs > 0) == (stats or q == 120_000)
+    ri, rd, _ = oracle_lib.knn(P, oracle_lib.build_tree(P), Qs, 8)
+    assert np.array_equal(i.cpu().numpy().reshape(ri.shape), ri)
+    assert np.array_equal(d.cpu().numpy().reshape(rd.shape).view(np.uint32), rd.view(np.uint32))
