@@ -163,3 +163,49 @@ def test_models_cost_nothing_where_rows_do_not_need_them(oracle_lib, q, stats):
     ri, rd, _ = oracle_lib.knn(P, oracle_lib.build_tree(P), Qs, 8)
     assert np.array_equal(i.cpu().numpy().reshape(ri.shape), ri)
     assert np.array_equal(d.cpu().numpy().reshape(rd.shape).view(np.uint32), rd.view(np.uint32))
+
+
+def _uniform(dim, n, q, seed):
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(seed)
+    return torch.rand((n, dim), generator=g, device="cuda:0"), torch.rand((q, dim), generator=g, device="cuda:0")
+
+
+@pytest.mark.parametrize("dim,k,n,line", [(3, 1, 200_000, 450_000), (3, 8, 300_000, 287_500), (4, 16, 262_144, 282_768),
+                                          (3, 32, 400_000, 350_000)])
+@pytest.mark.parametrize("host", [False, True])
+def test_even_points_line(dim, k, n, line, host):
+    """Both sides of the packets' line over evenly spread points (trees packed on
+    either side) equal the lane-by-lane kernel."""
+    import paper_2210_12859_amd as kd
+    P, Q = _uniform(dim, n, line, k)
+    tree = kd.kd_build_host(P.cpu().numpy()) if host else kd.kd_build(P)
+    for q in (line - 1, line):
+        print(f"[gpu] even line D={dim} k={k} Q={q} host={host}", flush=True)
+        i, d = kd.kd_knn(tree, Q[:q], k)
+        ri, rd, _ = kd.kd_knn_ex(tree, Q[:q], k, opts={"prune": 2})
+        assert torch.equal(i, ri) and torch.equal(d.view(torch.int32), rd.view(torch.int32))
+
+
+@pytest.mark.parametrize("host", [False, True])
+def test_even_points_are_not_slower_than_lane_by_lane(host):
+    """200,000 queries over 1M uniform points, k = 16: packets take 1.5 times as
+    long as the lanes."""
+    import paper_2210_12859_amd as kd
+    P, Q = _uniform(3, 1_000_000, 200_000, 1)
+    tree = kd.kd_build_host(P.cpu().numpy()) if host else kd.kd_build(P)
+
+    def ms(**kw):
+        best = np.inf
+        for _ in range(20):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            kd.kd_knn_ex(tree, Q, 16, **kw)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        return best
+
+    default, lanes = ms(), ms(opts={"prune": 2})
+    print(f"[gpu] even points host={host}: default {default:.3f} lanes {lanes:.3f} ms", flush=True)
+    assert default < 1.25 * lanes
