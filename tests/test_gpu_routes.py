@@ -209,3 +209,26 @@ def test_even_points_are_not_slower_than_lane_by_lane(host):
     default, lanes = ms(), ms(opts={"prune": 2})
     print(f"[gpu] even points host={host}: default {default:.3f} lanes {lanes:.3f} ms", flush=True)
     assert default < 1.25 * lanes
+
+
+@pytest.mark.parametrize("below", [0, 1])
+def test_batch_line_of_closest_points(below):
+    """A 3-D class of closest points on the packets' density, and one query below."""
+    import paper_2210_12859_amd as kd
+    jobs, want = [], []
+    for i, n in enumerate((40_000, 120_000, 80_001)):
+        q = n - n // 4 - (below if i == 1 else 0)
+        P, Q = _uniform(3, n, q, i)
+        tree = kd.kd_build(P)
+        want.append(kd.kd_knn_ex(tree, Q, 1, opts={"prune": 2})[:2])
+        jobs.append(dict(tree=tree, queries=Q, k=1, out_idx=torch.full((q,), -7, dtype=torch.int32, device="cuda:0"),
+                         out_d2=torch.full((q,), -7.0, dtype=torch.float32, device="cuda:0")))
+    print(f"[gpu] batch line below={below}", flush=True)
+    b = kd.Batch(jobs)
+    for _ in range(3):
+        b.run()
+        torch.cuda.synchronize()
+        for j, (wi, wd) in zip(jobs, want):
+            assert torch.equal(j["out_idx"], wi.view(-1)) and torch.equal(j["out_d2"], wd.view(-1))
+            j["out_idx"].fill_(-7)
+    b.close()
