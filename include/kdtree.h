@@ -23,7 +23,9 @@
  *    Query calls are asynchronous on it; the caller keeps every pointer alive
  *    and unmodified until the stream has reached the call.
  *  - Errors: every call returns a kd_status.  Arguments are validated before
- *    anything is enqueued; on error no output is touched.  kd_last_error()
+ *    anything is enqueued; on error no output is touched.  (Coordinates of
+ *    points on the device can only be checked there: kd_build does so while it
+ *    builds, and keeps nothing when one is NaN or infinite.)  kd_last_error()
  *    gives a thread-local message for the last non-OK status.  A device fault
  *    of an earlier asynchronous call surfaces as KD_EHIP from a later call.
  *  - Trees and models are immutable after creation; concurrent queries on
@@ -45,7 +47,7 @@ typedef void* kd_stream;             /* a hipStream_t */
 
 typedef enum {
     KD_OK = 0,
-    KD_EINVAL = -1,       /* bad argument; nothing enqueued */
+    KD_EINVAL = -1,       /* bad argument; nothing enqueued (kd_build: nothing kept) */
     KD_ENOMEM = -2,       /* device or host allocation failed */
     KD_EHIP = -3,         /* HIP runtime error (possibly from an earlier call) */
     KD_EUNSUPPORTED = -4  /* valid request this build does not implement */
@@ -121,11 +123,16 @@ typedef struct {
  * dim, and at every node the element of rank leftSize(|S|) of its subtree set
  * S ordered by (split coordinate, caller index) -- the unique tree once ties
  * are broken by index (Sec. 4 notes that any builder yields the same tree).
- *   points : device, float32 [N][dim]; read only.  NaN or +-inf -> KD_EINVAL.
+ *   points : device, float32 [N][dim]; read only.  NaN or +-inf -> KD_EINVAL,
+ *            found on the way: the build has run by then and is dropped.
  *   N      : 0 <= N <= KD_MAX_POINTS.  N = 0 gives an empty tree whose queries
  *            return all -1.
  *   dim    : 2, 3 or 4.
  *   out    : receives the tree; free with kd_tree_free.
+ * Device memory beside the points and the tree while it builds: 4 bytes a point
+ * and 4 x (2 dim + 4) to 4 x (5 dim + 3) + 2 (see kd_build_ex for the widest
+ * rule's); where that does not fit beside the tree, 4 x (2 dim + 4) before the
+ * tree is allocated.
  * Synchronises the stream (the build runs on the GPU; see kd_build_ex). */
 kd_status kd_build(const float* points, int64_t N, int dim, kd_stream stream, kd_tree* out);
 
@@ -149,7 +156,9 @@ kd_status kd_build(const float* points, int64_t N, int dim, kd_stream stream, kd
  * kd_knn_noalloc, kd_autotune, kd_radius_search and kd_box_search; the
  * learned-radius calls and batches return KD_EUNSUPPORTED for them.  Results
  * are the same exact kNN rows for either rule (the set of the k nearest by
- * (d2, index) does not depend on the tree); processed-node counts differ. */
+ * (d2, index) does not depend on the tree); processed-node counts differ.
+ * The widest rule's build takes 4 x (2 dim + 5) + 1 to 4 x (5 dim + 2) + 1 bytes
+ * a point of workspace. */
 kd_status kd_build_ex(const float* points, int64_t N, int dim, int split, kd_stream stream,
                       kd_tree* out);
 

@@ -279,8 +279,9 @@ __global__ void group_keys(const uint32_t* __restrict__ L, uint32_t R, size_t st
 // The levels from `top` on, one segment of that level per workgroup: its
 // points, at most MAX_SUB, are entries [start, start + size) of every list.
 // Bound by vector issue and the chain of LDS steps and barriers (3 a level).
-// 2047 points are the most whose lists leave a CU room for two workgroups; 16
-// waves a workgroup instead of 8: 55 -> 45 us at 300K points.
+// Two workgroups of 16 waves fill a CU; with 2047 points they take 27 (2-D) to 43
+// KB (4-D) of LDS each, with 4095 two would still fit in 2-D and 3-D, one in 4-D.
+// 16 waves a workgroup instead of 8: 55 -> 45 us at 300K points.
 constexpr int SUB_LEVELS = 11;
 constexpr int MAX_SUB = (1 << SUB_LEVELS) - 1;
 constexpr int SUB_ROWS = (MAX_SUB + 63) / 64;      // rows of 64 list entries

@@ -25,7 +25,9 @@
 // until some lane's share is full; all lanes then insert together.
 //
 // Bound by vector and scalar issue (a point costs about 20 instructions for all
-// 64 queries, an entered group about 150 and 18 for each child tested).  Bounding
+// 64 queries, an entered group about 150 and 18 for each child tested; in 3-D and
+// 4-D the compiler chooses between an item's point and box by address, through 28
+// and 48 bytes of private memory a lane).  Bounding
 // boxes of 16 regions each: with 32 a call takes up to 4 % longer, with 8 up to
 // 8 %, and without the test against every region 10 times as long on mixtures
 // (packets across clusters).  Lane by lane -> here, 1M 3-D points and queries,
