@@ -56,8 +56,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // (clusters) gain by.  1M points and queries, always 4 / always 2 / by candidates,
 // ms: 3-D, k = 1 mixture 0.410 / 0.381 / 0.368, k = 8 uniform 0.466 / 0.474 / 0.467,
 // mixture 0.668 / 0.660 / 0.648, clusters of many widths 1.237 / 1.197 / 1.143, k =
-// 32 clusters 3.436 / 3.275 / 3.195, k = 8 from a model's radii, mixture 1.772 /
-// 1.657 / 1.600; 4-D, k = 8 uniform 0.939 / 0.955 / 0.935, clusters 2.639 / 2.570 /
+// 32 clusters 3.436 / 3.275 / 3.195; 4-D, k = 8 uniform 0.939 / 0.955 / 0.935, clusters 2.639 / 2.570 /
 // 2.552, k = 16 uniform 1.328 / 1.349 / 1.317.  3 or 5 candidates instead of 4 are
 // within 1 % of it, 8 up to 2 % slower on clusters.
 constexpr uint32_t NPEND = 4;
